@@ -40,7 +40,8 @@
  *
  * Precision (kep_prec):
  *   KEP_FP64  plain binary64 everywhere: IEEE-rounded quotient (t - t0)/P,
- *             Danby iteration with a fixed 30 steps by default, binary64 sums.
+ *             Kepler's equation to the last bits of binary64 (the root that 30
+ *             Danby steps reach), binary64 sums.
  *   KEP_MIXED the paper's mixed precision (Sec. 5.1): the orbital phase
  *             (t - t0)/P reduced modulo one orbit is computed in binary64,
  *             Kepler's equation, the velocity and the planet sum in binary32
@@ -95,7 +96,9 @@ typedef struct kep_params {
 
 /* Options; pass NULL for the defaults.  A zero field means "default".
    fixed_iter  > 0: exactly this many Danby iterations for every solve.
-               = 0: KEP_FP64 uses 30 (the plain kernel); KEP_MIXED uses the
+               = 0: KEP_FP64 corrects a tabulated start in binary64 until the
+                    root no longer moves (what 30 plain steps give, which
+                    fixed_iter = 30 still runs); KEP_MIXED uses the
                     eccentricity schedule (2 iterations for e <= 0.8525, 3 up to
                     0.975, 4 up to 0.9955, 5 up to 0.999, then a convergence
                     test), derived offline for a 1e-9 rad worst-case error.
@@ -219,7 +222,7 @@ kep_status rv_eccentric_anomalies(const kep_obs *obs, const kep_params *par, flo
    not enough: KEP_MIXED keeps the binary64 phase and the binary32 Danby
    iteration and adds one binary64 Newton step against the binary64 mean
    anomaly (E to ~1e-11 rad), then forms the positions, residuals and sums in
-   binary64.  KEP_FP64 is the plain binary64 path (30 Danby steps by default).
+   binary64.  KEP_FP64 is the plain binary64 path.
    Domain: P > 0, 0 <= e < 1, finite parameters, sigma > 0, else NaN for that
    system.  Planes [n_pl][n_sys] as for kep_params; x0, y0 [n_sys] or NULL. */
 typedef struct kep_astro_obs {
@@ -279,7 +282,7 @@ typedef struct kep_plan kep_plan;   /* opaque; owned by the library */
    recorded).  May allocate and synchronises `stream`.  The plan keeps the
    other input pointers: their contents may change between calls, their
    addresses and sizes may not.  KEP_FP64 plans (the plain binary64 path of
-   rv_chisq, Sec. 5.1: IEEE quotient, 30 Danby steps by default) skip the
+   rv_chisq, Sec. 5.1: IEEE quotient, binary64 root) skip the
    autotuner and the graph: one wavefront per system over the work order,
    launched directly by both calls below; block_threads at most 256. */
 kep_status kep_plan_ragged(const kep_obs_csr *obs, const kep_params_csr *par, kep_prec prec,

@@ -35,8 +35,12 @@
    correction) in the first two bands, Danby's quartic one in the last; the kernels
    that hold the table take that one step only.
 
-Run:  python gen_tables.py         (rewrites kep_tables.h and kep_start_tab.h)
+4. sin and cos at the knots n/64, 0 <= n <= 208, correctly rounded to binary64
+   (kep_knots64.h): the binary64 path's sine and cosine of a root.
+
+Run:  python gen_tables.py         (rewrites the three headers)
       python gen_tables.py start   (kep_start_tab.h only)
+      python gen_tables.py knots   (kep_knots64.h only)
 """
 import os
 
@@ -279,6 +283,26 @@ def write_start_table(bands=START_BANDS, out=START_OUT):
         print(f"start table band {b}: far {far:.3e}, one step {err:.3e}")
 
 
+def write_knots(out=os.path.join(HERE, "kep_knots64.h")):
+    """kep_knots64.h: (sin, cos) of n/64, n = 0 .. 208 (3.25), from 30-digit values."""
+    half = 208
+    lines = [
+        "// Generated by gen_tables.py -- do not edit by hand.",
+        "#pragma once",
+        "",
+        "// (sin, cos) of n/64, n = 0 .. 208, correctly rounded to binary64.",
+        f"#define KEP_KNOTS64_HALF {half}",
+        "",
+        f"static __device__ const double kep_knots64[{half + 1}][2] = {{",
+    ]
+    for n in range(half + 1):
+        x = mp.mpf(n) / 64
+        lines.append(f"    {{{float(mp.sin(x)).hex()}, {float(mp.cos(x)).hex()}}},")
+    lines.append("};")
+    with open(out, "w") as f:
+        f.write("\n".join(lines) + "\n")
+
+
 def main():
     ymax = (np.pi / 2) ** 2 * 1.001
     grid = np.linspace(0.0, ymax, 3001)
@@ -328,11 +352,14 @@ def main():
         f.write("\n".join(lines) + "\n")
     print(open(OUT).read())
     write_start_table()
+    write_knots()
 
 
 if __name__ == "__main__":
     import sys
     if sys.argv[1:] == ["start"]:
         write_start_table()
+    elif sys.argv[1:] == ["knots"]:
+        write_knots()
     else:
         main()

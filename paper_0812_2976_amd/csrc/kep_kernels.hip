@@ -19,6 +19,7 @@
 #include "kep_internal.h"
 #include "kep_grad.h"
 #include "kep_policy.h"
+#include "kep_root64.h"
 
 namespace kep {
 
@@ -31,19 +32,26 @@ namespace kep {
 // held to four wavefronts it has none but ran 4% slower (c2 1.757 against
 // 1.688 ms).
 template <class Pol, int NCH>
-constexpr int dense_waves_per_simd() { return (Pol::kMixed && NCH <= 4) ? 5 : 1; }
+constexpr int dense_waves_per_simd()
+{
+    return NCH > 4 ? 1 : Pol::kMixed ? 5 : Pol::kTables == 2 ? 4 : 1;
+}
 
-// The mixed kernels start the Kepler solve from the table of kep_start_tab.h,
-// copied once into each block's LDS behind the records.
-template <class Pol, int MODE>
-constexpr bool dense_uses_table() { return Pol::kMixed; }
+// The mixed and the default binary64 kernels start the Kepler solve from the
+// table of kep_start_tab.h, copied once into each block's LDS behind the
+// records; the binary64 ones have the sin/cos knots behind it.
 
 __host__ __device__ inline size_t dense_table_offset(int wpb, int sb, int n_pl, size_t rec_size)
 {
     return ((size_t)wpb * sb * n_pl * rec_size + (size_t)wpb * sb * sizeof(int) + 15) & ~(size_t)15;
 }
 
-constexpr size_t kDenseTableBytes = sizeof(kep_start_tab);
+template <class Pol>
+constexpr size_t dense_table_bytes()
+{
+    static_assert(sizeof(kep_start_tab) % 16 == 0, "the knots after the table are 16-byte aligned");
+    return (Pol::kTables >= 1 ? sizeof(kep_start_tab) : 0) + (Pol::kTables == 2 ? kSc64Bytes : 0);
+}
 
 template <class Pol, int NCH, int MODE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dense_waves_per_simd<Pol, NCH>())))
@@ -59,11 +67,17 @@ k_dense(DenseArgs a)
     const int wib = uniform_int(threadIdx.x >> 6);
     Rec *recs = reinterpret_cast<Rec *>(smem) + (size_t)wib * a.sb * a.n_pl;
     int *sysbad = reinterpret_cast<int *>(smem + (size_t)wpb * a.sb * a.n_pl * sizeof(Rec)) + wib * a.sb;
-    // mixed velocities: the block's copy of the starting-value table after the records
+    // the block's copies of the starting-value table and the knots after the records
     const uint32_t *tab = nullptr;
-    if constexpr (dense_uses_table<Pol, MODE>()) {
+    const double2 *knots = nullptr;
+    if constexpr (Pol::kTables >= 1) {
         uint32_t *t = reinterpret_cast<uint32_t *>(smem + dense_table_offset(wpb, a.sb, a.n_pl, sizeof(Rec)));
-        load_start_table(t);
+        if constexpr (Pol::kTables == 2) {
+            double2 *k = reinterpret_cast<double2 *>(t + kTabWords);
+            load_knots64(k);
+            knots = k;
+        }
+        load_start_table(t);       // ends with the block barrier
         tab = t;
     }
 
@@ -155,7 +169,7 @@ k_dense(DenseArgs a)
                     for (int j = 0; j < a.n_pl; ++j) {
 #pragma unroll
                         for (int c = 0; c < NCH; ++c) Pol::model_init(m[c]);
-                        pol_add_planet<Pol, NCH>(recs[s * a.n_pl + j], o, m, a, tab);
+                        pol_add_planet<Pol, NCH>(recs[s * a.n_pl + j], o, m, a, tab, knots);
                         float *row = a.dv + ((int64_t)j * a.n_sys + sys) * a.n_obs;
 #pragma unroll
                         for (int c = 0; c < NCH; ++c) {
@@ -170,7 +184,7 @@ k_dense(DenseArgs a)
                 }
 #pragma unroll
                 for (int c = 0; c < NCH; ++c) Pol::model_init(m[c]);
-                for (int j = 0; j < a.n_pl; ++j) pol_add_planet<Pol, NCH>(recs[s * a.n_pl + j], o, m, a, tab);
+                for (int j = 0; j < a.n_pl; ++j) pol_add_planet<Pol, NCH>(recs[s * a.n_pl + j], o, m, a, tab, knots);
                 if (MODEL) {
 #pragma unroll
                     for (int c = 0; c < NCH; ++c) {
@@ -257,10 +271,15 @@ __global__ void __launch_bounds__(256) k_chisq_from_dv(DenseArgs a)
 // ------------------------------------------------------------------ Kepler only
 // Standalone Kepler solve (the paper's Kepler-only mode): one lane per pair.
 // M is reduced to [-pi, pi] with 2 pi as a double-double; the root is returned
-// on the input's branch.  Mixed: from the starting-value table (the block's
-// LDS copy) and one quartic step where e <= KEP_TAB_EMAX, else the schedule.
-template <bool MIXED>
-__device__ __forceinline__ double kepler_one(double M, double e, int fixed, int max_iter, const uint32_t *tab)
+// on the input's branch.  kKepMixed: from the starting-value table (the block's
+// LDS copy) and one quartic step where e <= KEP_TAB_EMAX, else the schedule;
+// kKepRoot64: that binary32 value corrected in binary64 (kep_root64.h);
+// kKepDanby64: Danby's plain binary64 iteration (fixed_iter != 0).
+enum { kKepDanby64 = 0, kKepMixed = 1, kKepRoot64 = 2 };
+
+template <int KIND>
+__device__ __forceinline__ double kepler_one(double M, double e, int fixed, int max_iter, const uint32_t *tab,
+                                             const double2 *knots)
 {
     const bool ok = isfinite(M) && isfinite(e) && e >= 0.0 && e < 1.0;
     if (!ok) { M = 0.0; e = 0.0; }
@@ -268,14 +287,20 @@ __device__ __forceinline__ double kepler_one(double M, double e, int fixed, int 
     double Mr = fma(-kq, kTwoPiHi, M);
     Mr = fma(-kq, kTwoPiLo, Mr);
     double E;
-    if (MIXED) {
+    if (KIND == kKepDanby64) {
+        E = kepler64(Mr, e, Mr >= 0.0 ? 1.0 : -1.0, fixed, max_iter);
+    } else {
         const Ecc32 k = make_ecc32(e);
         const int niter = fixed > 0 ? fixed : sched32(k.e);
+        const TabPlace tp = table_place(e, fixed <= 0);
         float sE, omcE;   // unused here: the standalone solve returns E only
-        E = (double)kepler32_start((float)Mr, k, table_place(e, fixed <= 0), tab, niter, max_iter, fixed > 0, sE,
-                                   omcE);
-    } else {
-        E = kepler64(Mr, e, Mr >= 0.0 ? 1.0 : -1.0, fixed, max_iter);
+        const float E32 = kepler32_start((float)Mr, k, tp, tab, niter, max_iter, fixed > 0, sE, omcE);
+        E = (double)E32;
+        if (KIND == kKepRoot64) {
+            Root64 r;
+            refine_root64(e, E32, Mr, tp.toff < 0, knots, r);
+            E = r.E;
+        }
     }
     E = fma(kq, kTwoPiHi, E);
     E = fma(kq, kTwoPiLo, E);
@@ -285,14 +310,20 @@ __device__ __forceinline__ double kepler_one(double M, double e, int fixed, int 
 // Each thread takes KU pairs per tile (KU x blockDim consecutive pairs per
 // block), issuing all of their loads before solving, so that more memory
 // requests are in flight than one pair per thread would allow.
-template <bool MIXED, int KU>
+template <int KIND, int KU>
 __global__ void __launch_bounds__(256) k_kepler(const double *__restrict__ Mv, const double *__restrict__ ev,
                                                double *__restrict__ Ev, int64_t n, int fixed, int max_iter)
 {
     const uint32_t *tab = nullptr;
-    if constexpr (MIXED) {
+    const double2 *knots = nullptr;
+    if constexpr (KIND == kKepRoot64) {
+        __shared__ double2 knots_s[kSc64Knots];
+        load_knots64(knots_s);
+        knots = knots_s;
+    }
+    if constexpr (KIND != kKepDanby64) {
         __shared__ uint32_t tab_s[kTabWords];    // Kepler starting values
-        load_start_table(tab_s);
+        load_start_table(tab_s);                 // ends with the block barrier
         tab = tab_s;
     }
     const int64_t tile = (int64_t)blockDim.x * KU;
@@ -309,7 +340,7 @@ __global__ void __launch_bounds__(256) k_kepler(const double *__restrict__ Mv, c
 #pragma unroll
         for (int u = 0; u < KU; ++u) {
             const int64_t i = base + (int64_t)u * blockDim.x;
-            const double E = kepler_one<MIXED>(M[u], e[u], fixed, max_iter, tab);
+            const double E = kepler_one<KIND>(M[u], e[u], fixed, max_iter, tab, knots);
             if (i < n) __builtin_nontemporal_store(E, Ev + i);
         }
     }
@@ -922,10 +953,12 @@ hipError_t launch_kepler_solve(const double *M, const double *e, double *E, int6
     const int64_t cap = (int64_t)device_cu_count() * per_cu;
     const int grid = (int)(need < cap ? need : cap);
     if (prec == Prec::Mixed)
-        hipLaunchKernelGGL((k_kepler<true, KU>), dim3(grid), dim3(block), 0, st, M, e, E, n, fixed_iter, max_iter);
+        hipLaunchKernelGGL((k_kepler<kKepMixed, KU>), dim3(grid), dim3(block), 0, st, M, e, E, n, fixed_iter, max_iter);
+    else if (fixed_iter == 0)
+        hipLaunchKernelGGL((k_kepler<kKepRoot64, KU>), dim3(grid), dim3(block), 0, st, M, e, E, n, 0, max_iter);
     else
-        hipLaunchKernelGGL((k_kepler<false, KU>), dim3(grid), dim3(block), 0, st, M, e, E, n,
-                           fixed_iter == 0 ? 30 : (fixed_iter < 0 ? 0 : fixed_iter), max_iter);
+        hipLaunchKernelGGL((k_kepler<kKepDanby64, KU>), dim3(grid), dim3(block), 0, st, M, e, E, n,
+                           fixed_iter < 0 ? 0 : fixed_iter, max_iter);
     return hipGetLastError();
 }
 
@@ -935,14 +968,17 @@ static hipError_t launch_dense_t(DenseArgs a, LaunchShape shape, hipStream_t st)
     const int block = shape.block > 0 ? shape.block : 256;
     const int wpb = block / 64;
     const size_t rec_bytes = (size_t)wpb * a.n_pl * sizeof(typename Pol::Rec) + (size_t)wpb * sizeof(int);
-    constexpr bool table = dense_uses_table<Pol, MODE>();
+    constexpr bool table = Pol::kTables >= 1;
     auto lds_of = [&](int64_t sb) {
-        return table ? dense_table_offset(wpb, (int)sb, a.n_pl, sizeof(typename Pol::Rec)) + kDenseTableBytes
+        return table ? dense_table_offset(wpb, (int)sb, a.n_pl, sizeof(typename Pol::Rec)) + dense_table_bytes<Pol>()
                      : rec_bytes * (size_t)sb;
     };
     // systems per setup batch: at most kMaxSB and at most 48 KiB of LDS per block
-    // (with the table, 32 KiB: five blocks of four wavefronts share a CU's 160 KiB)
-    const int64_t budget = table ? (int64_t)(32 * 1024) - (int64_t)kDenseTableBytes - 16 : (int64_t)(48 * 1024);
+    // (with the table, 32 KiB: five blocks of four wavefronts share a CU's 160 KiB;
+    // with the knots too, 40 KiB and four blocks)
+    const int64_t budget = table ? (int64_t)((Pol::kTables == 2 ? 40 : 32) * 1024) -
+                                       (int64_t)dense_table_bytes<Pol>() - 16
+                                 : (int64_t)(48 * 1024);
     int64_t sb_cap = budget / (int64_t)rec_bytes;
     sb_cap = sb_cap < 1 ? 1 : (sb_cap > kMaxSB ? kMaxSB : sb_cap);
     // a multiple of 16 systems reads whole 128-byte lines of every parameter plane:
@@ -955,6 +991,7 @@ static hipError_t launch_dense_t(DenseArgs a, LaunchShape shape, hipStream_t st)
     if (nch_needed <= 1) { kern = k_dense<Pol, 1, MODE>; nch = 1; }
     else if (nch_needed <= 2) { kern = k_dense<Pol, 2, MODE>; nch = 2; }
     else if (nch_needed <= 4) { kern = k_dense<Pol, 4, MODE>; nch = 4; }
+    else if constexpr (Pol::kTables == 2) { kern = k_dense<Pol, 4, MODE>; nch = 4; }   // eight: 256 VGPRs, one wavefront
     else { kern = k_dense<Pol, 8, MODE>; nch = 8; }
     int per_cu = shape.blocks_per_cu;
     if (per_cu <= 0) {
@@ -985,6 +1022,8 @@ hipError_t launch_dense(DenseArgs a, Prec prec, bool model, LaunchShape shape, h
     if (model && a.n_obs <= 0) return hipSuccess;
     if (prec == Prec::Mixed)
         return model ? launch_dense_t<PolMixed, kModel>(a, shape, st) : launch_dense_t<PolMixed, kChi2>(a, shape, st);
+    if (a.fixed_iter == 0)
+        return model ? launch_dense_t<Pol64R, kModel>(a, shape, st) : launch_dense_t<Pol64R, kChi2>(a, shape, st);
     return model ? launch_dense_t<Pol64, kModel>(a, shape, st) : launch_dense_t<Pol64, kChi2>(a, shape, st);
 }
 

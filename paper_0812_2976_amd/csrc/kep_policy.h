@@ -166,6 +166,7 @@ struct ObsMixed {
 
 struct PolMixed {
     static constexpr bool kMixed = true;
+    static constexpr int kTables = 1;      // the starting-value table in each block's LDS
     using Rec = RecMixed;
     using Obs = ObsMixed;
     // the planet sum in binary64: each binary32 velocity is added exactly (two
@@ -380,6 +381,7 @@ struct Obs64 {
 
 struct Pol64 {
     static constexpr bool kMixed = false;
+    static constexpr int kTables = 0;
     using Rec = Rec64;
     using Obs = Obs64;
     struct ModelAcc { double s; };
@@ -424,7 +426,8 @@ struct Pol64 {
         o.w = 1.0;
     }
 
-    // Plain binary64 (the paper's double-precision variant): IEEE quotient
+    // Danby's plain iteration (fixed_iter != 0; Pol64R in kep_root64.h has the
+    // default): IEEE quotient
     // (t - t0)/P, exact fraction, M = 2 pi frac + M0 in [0, 2 pi), Danby's
     // iteration, then v = K b (b cos w cos E - sin w sin E) / (1 - e cos E).
     template <int NCH>
@@ -467,16 +470,17 @@ struct Pol64 {
     static __device__ __forceinline__ double chi_value(const ChiAcc &x) { return x; }
 };
 
-// Iteration count of the plain binary64 kernel: fixed_iter > 0 as given,
-// 0 -> the fixed 30 steps of the plain kernel, < 0 -> schedule + convergence test.
+// Iteration count of Danby's plain binary64 iteration: fixed_iter > 0 as given,
+// 0 -> 30, < 0 -> schedule + convergence test.
 __device__ __forceinline__ int fixed64(int fixed_iter) { return fixed_iter > 0 ? fixed_iter : (fixed_iter == 0 ? 30 : 0); }
 
 template <class Pol, int NCH>
 __device__ __forceinline__ void pol_add_planet(const typename Pol::Rec &r, const typename Pol::Obs (&o)[NCH],
                                                typename Pol::ModelAcc (&m)[NCH], const DenseArgs &a,
-                                               const uint32_t *tab = nullptr)
+                                               const uint32_t *tab = nullptr, const double2 *knots = nullptr)
 {
-    if constexpr (Pol::kMixed) Pol::template add_planet<NCH>(r, o, m, a.max_iter, 0, tab);
+    if constexpr (Pol::kTables == 2) Pol::template add_planet<NCH>(r, o, m, a.max_iter, tab, knots);
+    else if constexpr (Pol::kMixed) Pol::template add_planet<NCH>(r, o, m, a.max_iter, 0, tab);
     else Pol::template add_planet<NCH>(r, o, m, a.max_iter, fixed64(a.fixed_iter));
 }
 
