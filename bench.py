@@ -140,7 +140,8 @@ def op_fractions(e):
 
 # The sources each timed kernel is compiled from (its counter summaries under
 # profiles/ record their hash; a summary taken on other sources is not used).
-DENSE_FILES = ("kep_kernels.hip", "kep_policy.h", "kep_device.h", "kep_tables.h", "kep_start_tab.h", "kep_grad.h")
+DENSE_FILES = ("kep_kernels.hip", "kep_policy.h", "kep_device.h", "kep_tables.h", "kep_start_tab.h", "kep_grad.h",
+               "kep_root64.h", "kep_knots64.h")
 ADJOINT_FILES = ("kep_adjoint.hip", "kep_grad.h", "kep_policy.h", "kep_device.h", "kep_tables.h", "kep_start_tab.h")
 
 

@@ -196,7 +196,9 @@ static kep_status dense_grad(const kep_obs *obs, const kep_params *par, double *
     if (!out || !grad) return fail(KEP_ERR_ARG, "%s: %s and grad must not be NULL", fn, nll ? "nll" : "chi2");
     if (kep_status s = check_device(fn)) return s;
     kep::DenseArgs a = make_dense(obs, par, o, out, grad);
-    return launch_status(kep::launch_dense_grad(a, to_prec(prec), nll, o.shape, (hipStream_t)stream), fn);
+    return launch_status(prec == KEP_MIXED ? kep::launch_grad_mixed(a, nll, o.shape, (hipStream_t)stream)
+                                           : kep::launch_grad64(a, nll, o.shape, (hipStream_t)stream),
+                         fn);
 }
 
 kep_status rv_chisq_grad(const kep_obs *obs, const kep_params *par, double *chi2, double *grad, kep_prec prec,
@@ -624,7 +626,7 @@ kep_status kep_plan_ragged(const kep_obs_csr *obs, const kep_params_csr *par, ke
         a.sb = 1;
         a.gmax = 4;
         a.n_items = n_sys;
-        p->grid = n_sys > 0 ? kep::ragged64_grid(p->shape, n_sys) : 0;
+        p->grid = n_sys > 0 ? kep::ragged64_grid(p->shape, n_sys, o.fixed_iter) : 0;
         *out = p;
         return KEP_OK;
     }

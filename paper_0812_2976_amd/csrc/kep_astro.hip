@@ -19,14 +19,20 @@
 #include "kep_grad.h"
 #include "kep_internal.h"
 #include "kep_policy.h"
+#include "kep_root64.h"
 
 namespace kep {
 
 namespace {
 
+// Kepler solves of the astrometric kernels: kAstroDanby64, Danby's plain
+// binary64 iteration (fixed_iter != 0); kAstroMixed; kAstroRoot64, the binary64
+// root of kep_root64.h (the binary64 default).
+enum { kAstroDanby64 = 0, kAstroMixed = 1, kAstroRoot64 = 2 };
+
 struct AstroRec {          // one per (system, planet)
-    Phase64 ph;            // P, 1/P, fract(M0/(2 pi) + 1/2)
-    double M0, e, b;       // b = sqrt(1 - e^2)
+    Phase64 ph;            // P, 1/P, fract(M0/(2 pi) + 1/2); binary64: Phase64c's P, 1/P, M0 in [-pi, pi]
+    double e, b;           // b = sqrt(1 - e^2)
     double A, B, F, G;
     Ecc32 k;
     TabPlace tp;           // place in the starting-value table (toff -1: the paper's guess)
@@ -38,14 +44,19 @@ struct AstroObs {
     bool in, ok;
 };
 
+template <int KIND>
 __device__ __forceinline__ bool astro_setup(const AstroArgs &a, int64_t p, AstroRec &r)
 {
     double P = a.P[p], e = a.e[p], M0 = a.M0[p], A = a.A[p], B = a.B[p], F = a.F[p], G = a.G[p];
     const bool ok = isfinite(P) && P > 0.0 && isfinite(e) && e >= 0.0 && e < 1.0 && isfinite(M0) &&
                     isfinite(A) && isfinite(B) && isfinite(F) && isfinite(G);
     if (!ok) { P = 1.0; e = 0.0; M0 = 0.0; A = B = F = G = 0.0; }
-    r.ph = make_phase64(P, M0);
-    r.M0 = M0;
+    if constexpr (KIND == kAstroMixed) {
+        r.ph = make_phase64(P, M0);
+    } else {
+        const Phase64c p64 = make_phase64c(P, M0);
+        r.ph = Phase64{p64.P, p64.rP, p64.M0c};
+    }
     r.e = e;
     r.b = sqrt((1.0 - e) * (1.0 + e));
     r.A = A;
@@ -87,19 +98,28 @@ __device__ __forceinline__ void astro_cs_mixed(const AstroRec &r, double tt, int
     sE = s + d * c - hd2 * s;
 }
 
-// Plain binary64: IEEE quotient, M in [0, 2 pi), Danby iteration (kepler64).
-__device__ __forceinline__ void astro_cs_f64(const AstroRec &r, double tt, int fixed, int max_iter, double &cE,
-                                             double &sE)
+// Binary64: the centred mean anomaly of the IEEE quotient, then Danby's plain
+// iteration or the corrected binary32 root.
+template <int KIND>
+__device__ __forceinline__ void astro_cs_f64(const AstroRec &r, double tt, int fixed, int max_iter, const uint32_t *tab,
+                                             const double2 *knots, double &cE, double &sE)
 {
-    const double q = tt / r.ph.P;
-    const double phi = q - floor(q);
-    double M = fma(kTwoPi, phi, r.M0);
-    M = M - kTwoPi * floor(M * kInvTwoPi);
-    const double E = kepler64(M, r.e, M < kPi ? 1.0 : -1.0, fixed, max_iter);
-    sincos(E, &sE, &cE);
+    double q;
+    const double M = mean_anomaly64c(tt, Phase64c{r.ph.P, r.ph.rP, r.ph.m0h}, q);
+    if constexpr (KIND == kAstroRoot64) {
+        float s32, omc32;
+        const float E32 = kepler32_start((float)M, r.k, r.tp, tab, r.niter, max_iter, false, s32, omc32);
+        Root64 g;
+        refine_root64(r.e, E32, M, r.tp.toff < 0, knots, g);
+        cE = g.c;
+        sE = g.s;
+    } else {
+        const double E = kepler64(M, r.e, M >= 0.0 ? 1.0 : -1.0, fixed, max_iter);
+        sincos(E, &sE, &cE);
+    }
 }
 
-template <bool MIXED, int NCH, bool MODEL>
+template <int KIND, int NCH, bool MODEL>
 __global__ void __launch_bounds__(256) k_astro(AstroArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -109,13 +129,13 @@ __global__ void __launch_bounds__(256) k_astro(AstroArgs a)
     const int npl = a.n_pl;
     AstroRec *recs = reinterpret_cast<AstroRec *>(smem) + (size_t)wib * a.sb * npl;
     int *sysbad = reinterpret_cast<int *>(smem + (size_t)wpb * a.sb * npl * sizeof(AstroRec)) + wib * a.sb;
-    // mixed: the block's copy of the Kepler starting-value table
+    // the block's copies of the Kepler starting-value table and the sin/cos knots
     const uint32_t *tab = nullptr;
     const double2 *knots = nullptr;
-    if constexpr (MIXED) {
+    if constexpr (KIND != kAstroDanby64) {
         __shared__ uint32_t tab_s[kTabWords];
         __shared__ double2 knots_s[kSc64Knots];
-        fill_sincos64_knots(knots_s);
+        load_knots64(knots_s);
         load_start_table(tab_s);        // ends with the block barrier
         tab = tab_s;
         knots = knots_s;
@@ -166,7 +186,7 @@ __global__ void __launch_bounds__(256) k_astro(AstroArgs a)
                 bool ok = isfinite(a.t0);
                 for (int j = 0; j < npl; ++j) {
                     AstroRec r;
-                    ok = astro_setup(a, (int64_t)j * a.n_sys + sys, r) && ok;
+                    ok = astro_setup<KIND>(a, (int64_t)j * a.n_sys + sys, r) && ok;
                     recs[lane * npl + j] = r;
                 }
                 if (a.x0) ok = ok && isfinite(a.x0[sys]);
@@ -192,8 +212,8 @@ __global__ void __launch_bounds__(256) k_astro(AstroArgs a)
                     for (int c = 0; c < NCH; ++c) {
                         if (!o[c].in) continue;
                         double cE, sE;
-                        if (MIXED) astro_cs_mixed(r, o[c].t - a.t0, a.max_iter, tab, knots, cE, sE);
-                        else astro_cs_f64(r, o[c].t - a.t0, fixed, a.max_iter, cE, sE);
+                        if (KIND == kAstroMixed) astro_cs_mixed(r, o[c].t - a.t0, a.max_iter, tab, knots, cE, sE);
+                        else astro_cs_f64<KIND>(r, o[c].t - a.t0, fixed, a.max_iter, tab, knots, cE, sE);
                         const double X = cE - r.e, Y = r.b * sE;
                         ra[c] = fma(r.B, X, fma(r.G, Y, ra[c]));
                         dec[c] = fma(r.A, X, fma(r.F, Y, dec[c]));
@@ -223,25 +243,25 @@ __global__ void __launch_bounds__(256) k_astro(AstroArgs a)
     }
 }
 
-template <bool MIXED, bool MODEL>
+template <int KIND, bool MODEL>
 hipError_t launch_astro_t(AstroArgs a, LaunchShape shape, hipStream_t st)
 {
     const int block = shape.block > 0 ? shape.block : 256;
     const int wpb = block / 64;
     const size_t rec_bytes = (size_t)wpb * a.n_pl * sizeof(AstroRec) + (size_t)wpb * sizeof(int);
-    // records and (mixed) the block's tables within 32 KiB, so that five blocks
+    // records and the block's tables within 31.25 KiB, so that five blocks
     // of four wavefronts share a CU's 160 KiB (the binary32-iteration kernels
     // fit five wavefronts per SIMD in registers; at 1,048,576 x 2 x 128,
     // 48 KiB and three blocks: 1.15 ms, 40 KiB: 1.08 ms, 32 KiB: 1.06 ms)
-    const int64_t tables = MIXED ? (int64_t)(sizeof(kep_start_tab) + kSc64Bytes) : 0;
-    int64_t sb_cap = ((int64_t)(32 * 1024) - tables) / (int64_t)rec_bytes;
+    const int64_t tables = KIND != kAstroDanby64 ? (int64_t)(sizeof(kep_start_tab) + kSc64Bytes) : 0;
+    int64_t sb_cap = (lds_budget(5) - tables) / (int64_t)rec_bytes;
     sb_cap = sb_cap < 1 ? 1 : (sb_cap > kMaxSB ? kMaxSB : sb_cap);
     const int nch_needed = (int)((a.n_obs + 63) / 64);
     void (*kern)(AstroArgs);
     int nch;
-    if (nch_needed <= 1) { kern = k_astro<MIXED, 1, MODEL>; nch = 1; }
-    else if (nch_needed <= 2) { kern = k_astro<MIXED, 2, MODEL>; nch = 2; }
-    else { kern = k_astro<MIXED, 4, MODEL>; nch = 4; }
+    if (nch_needed <= 1) { kern = k_astro<KIND, 1, MODEL>; nch = 1; }
+    else if (nch_needed <= 2) { kern = k_astro<KIND, 2, MODEL>; nch = 2; }
+    else { kern = k_astro<KIND, 4, MODEL>; nch = 4; }
     int per_cu = shape.blocks_per_cu;
     if (per_cu <= 0) {
         per_cu = cached_occupancy((const void *)kern, block, rec_bytes * (size_t)sb_cap);
@@ -269,8 +289,10 @@ hipError_t launch_astro(AstroArgs a, Prec prec, bool model, LaunchShape shape, h
     if (a.n_sys <= 0) return hipSuccess;
     if (model && a.n_obs <= 0) return hipSuccess;
     if (prec == Prec::Mixed)
-        return model ? launch_astro_t<true, true>(a, shape, st) : launch_astro_t<true, false>(a, shape, st);
-    return model ? launch_astro_t<false, true>(a, shape, st) : launch_astro_t<false, false>(a, shape, st);
+        return model ? launch_astro_t<kAstroMixed, true>(a, shape, st) : launch_astro_t<kAstroMixed, false>(a, shape, st);
+    if (a.fixed_iter == 0)
+        return model ? launch_astro_t<kAstroRoot64, true>(a, shape, st) : launch_astro_t<kAstroRoot64, false>(a, shape, st);
+    return model ? launch_astro_t<kAstroDanby64, true>(a, shape, st) : launch_astro_t<kAstroDanby64, false>(a, shape, st);
 }
 
 }  // namespace kep

@@ -17,6 +17,7 @@
 #include "kep_internal.h"
 #include "kep_philox.h"
 #include "kep_policy.h"
+#include "kep_root64.h"
 
 namespace kep {
 
@@ -115,11 +116,17 @@ __global__ void __launch_bounds__(256) k_demc_half(DenseArgs a, DemcArgs m, int 
     int *okpl_l = reinterpret_cast<int *>(r12_l + 2 * sb);
     int *bad_l = okpl_l + sb * npl;
     int *supp_l = bad_l + sb;
-    // mixed: the block's copy of the Kepler starting-value table after the wave slices
+    // the block's copies of the Kepler starting-value table and the knots after the wave slices
     const uint32_t *tab = nullptr;
-    if constexpr (Pol::kMixed) {
+    const double2 *knots = nullptr;
+    if constexpr (Pol::kTables >= 1) {
         uint32_t *t = reinterpret_cast<uint32_t *>(smem + (size_t)wpb * demc_lds_per_wave(sb, npl, d, sizeof(Rec)));
-        load_start_table(t);
+        if constexpr (Pol::kTables == 2) {
+            double2 *k = reinterpret_cast<double2 *>(t + kTabWords);
+            load_knots64(k);
+            knots = k;
+        }
+        load_start_table(t);       // ends with the block barrier
         tab = t;
     }
 
@@ -216,7 +223,7 @@ __global__ void __launch_bounds__(256) k_demc_half(DenseArgs a, DemcArgs m, int 
                 ModelAcc mm[NCH];
 #pragma unroll
                 for (int c = 0; c < NCH; ++c) Pol::model_init(mm[c]);
-                for (int j = 0; j < npl; ++j) pol_add_planet<Pol, NCH>(recs[s * npl + j], o, mm, a, tab);
+                for (int j = 0; j < npl; ++j) pol_add_planet<Pol, NCH>(recs[s * npl + j], o, mm, a, tab, knots);
 #pragma unroll
                 for (int c = 0; c < NCH; ++c) {
                     if (o[c].in) {
@@ -251,7 +258,7 @@ static hipError_t launch_demc_half_t(DemcArgs m, DenseArgs a, int h, LaunchShape
     const int block = shape.block > 0 ? shape.block : 256;
     const int wpb = block / 64;
     const size_t rec = sizeof(typename Pol::Rec);
-    const size_t table = Pol::kMixed ? sizeof(kep_start_tab) : 0;
+    const size_t table = (Pol::kTables >= 1 ? sizeof(kep_start_tab) : 0) + (Pol::kTables == 2 ? kSc64Bytes : 0);
     int sb_cap = kMaxSB;
     while (sb_cap > 1 && (size_t)wpb * demc_lds_per_wave(sb_cap, a.n_pl, m.d, rec) + table > 48 * 1024) sb_cap /= 2;
     const int nch_needed = (int)((a.n_obs + 63) / 64);
@@ -259,6 +266,7 @@ static hipError_t launch_demc_half_t(DemcArgs m, DenseArgs a, int h, LaunchShape
     if (nch_needed <= 1) kern = k_demc_half<Pol, 1>;
     else if (nch_needed <= 2) kern = k_demc_half<Pol, 2>;
     else if (nch_needed <= 4) kern = k_demc_half<Pol, 4>;
+    else if constexpr (Pol::kTables == 2) kern = k_demc_half<Pol, 4>;   // eight: 246 VGPRs
     else kern = k_demc_half<Pol, 8>;
     int per_cu = shape.blocks_per_cu;
     if (per_cu <= 0) {
@@ -291,8 +299,9 @@ hipError_t launch_demc_half(DemcArgs m, DenseArgs a, Prec prec, int h, LaunchSha
     a.out = nullptr;
     a.grad = nullptr;
     a.dv = nullptr;
-    return prec == Prec::Mixed ? launch_demc_half_t<PolMixed>(m, a, h, shape, st)
-                               : launch_demc_half_t<Pol64>(m, a, h, shape, st);
+    if (prec == Prec::Mixed) return launch_demc_half_t<PolMixed>(m, a, h, shape, st);
+    return a.fixed_iter == 0 ? launch_demc_half_t<Pol64R>(m, a, h, shape, st)
+                             : launch_demc_half_t<Pol64>(m, a, h, shape, st);
 }
 
 hipError_t launch_demc_chisq(DemcArgs a, DenseArgs base, Prec prec, LaunchShape shape, hipStream_t st)

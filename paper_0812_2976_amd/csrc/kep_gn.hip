@@ -26,6 +26,7 @@
 #include "kep_grad.h"
 #include "kep_internal.h"
 #include "kep_policy.h"
+#include "kep_root64.h"
 
 namespace kep {
 
@@ -46,48 +47,75 @@ __device__ __forceinline__ void gn_store(const DenseArgs &a, double *jtwr, doubl
 }
 
 // ------------------------------------------------------------------ binary64
-template <int NB>
-__host__ __device__ constexpr int gn64_stride() { return 16 * NB + 1; }   // odd row length: staggers LDS banks
+// Binary64 path (k_gn64): one chunk of 64 observations at a time, each lane's
+// row of sqrt(w) [J | 1 | r] in the wavefront's column-major tile (the layout
+// and the block products of the mixed path, in binary64), four observations per
+// v_mfma_f64_16x16x4_f64.  The binary64 product returns row l/16 + 4 q of its
+// block in accumulator q (the binary32 one row 4 (l/16) + q).  ROOT: the default
+// step count (kep_root64.h; its starting-value table is read through the cache,
+// as in the mixed kernel, the sin/cos knots from LDS); else Danby's plain
+// iteration.
+//
+// What bounds it: at 262,144 x 4 x 256 the products (64 cycles each, two per
+// four observations) and the row arithmetic take about the same time and add
+// up, as in the mixed kernel.
+constexpr int kGn64Col = 66;   // 64 observations + 2: consecutive columns start 4 banks apart
 
-template <int NB>
+template <int NPL>
 __host__ __device__ inline size_t gn64_lds_per_wave()
 {
-    const size_t b = (size_t)64 * gn64_stride<NB>() * sizeof(double) + (size_t)kMaxPl * sizeof(GradPlanet<double>);
-    return (b + 15) & ~(size_t)15;
+    return ((size_t)(5 * NPL + 2) * kGn64Col + 0) * sizeof(double) + ((NPL * sizeof(RecG64) + 15) & ~(size_t)15);
 }
 
-template <int NB>
-__global__ void __launch_bounds__(256) k_gn64(DenseArgs a, double *jtwr, double *jtwj)
+template <bool ROOT, int NPL>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NPL <= 6 ? 3 : 2)))
+k_gn64(DenseArgs a, double *jtwr, double *jtwj)
 {
-    constexpr int NCOL = 16 * NB;
-    constexpr int STRIDE = gn64_stride<NB>();
-    constexpr int NPAIR = NB * (NB + 1) / 2;
+    constexpr int NC = 5 * NPL + 2;          // parameters, offset, residual
+    constexpr int NP = NC - 1;
+    constexpr int NB = (NC + 15) / 16;
+    constexpr bool TWO = NC > 16 && NC <= 24;
+    constexpr int GX = NC - 16;
+    constexpr int NOP = TWO ? 3 : NB;
+    constexpr int NPAIR = TWO ? 2 : NB * (NB + 1) / 2;
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = __lane_id();
     const int wpb = blockDim.x >> 6;
     const int wib = uniform_int(threadIdx.x >> 6);
-    unsigned char *mine = smem + (size_t)wib * gn64_lds_per_wave<NB>();
+    unsigned char *mine = smem + (size_t)wib * gn64_lds_per_wave<NPL>();
     double *T = reinterpret_cast<double *>(mine);
-    GradPlanet<double> *pl = reinterpret_cast<GradPlanet<double> *>(mine + (size_t)64 * STRIDE * sizeof(double));
+    RecG64 *pl = reinterpret_cast<RecG64 *>(T + (size_t)NC * kGn64Col);
+    const double2 *knots = nullptr;
+    if constexpr (ROOT) {
+        double2 *k = reinterpret_cast<double2 *>(smem + (size_t)wpb * gn64_lds_per_wave<NPL>());
+        load_knots64(k);
+        __syncthreads();
+        knots = k;
+    }
 
-    const int npl = a.n_pl;
-    const int np = 5 * npl + 1;
     const int fixed = fixed64(a.fixed_iter);
     const bool has_jit = a.jitter != nullptr;
     const int n_chunks = (int)((a.n_obs + 63) / 64);
     const int64_t n_waves = (int64_t)gridDim.x * wpb;
     const double nan = __builtin_nan("");
-    double *row = T + lane * STRIDE;
-    // padding columns np + 1 .. NCOL - 1 stay zero for the whole launch
-    for (int c = np + 1; c < NCOL; ++c) row[c] = 0.0;
+    double *col = T + lane;
+    const int li = lane & 15;
+    const double *src[NOP];                  // this lane's operand columns (as k_gn_obs)
+#pragma unroll
+    for (int b = 0; b < NOP; ++b) {
+        int c;
+        if constexpr (TWO) c = b == 0 ? li : b == 1 ? (li < GX ? li : (li + 8 < NC ? li + 8 : li)) : GX + li;
+        else c = 16 * b + li < NC ? 16 * b + li : NC - 1;
+        src[b] = T + c * kGn64Col + 16 * (lane >> 4);
+    }
 
     for (int64_t sys = (int64_t)blockIdx.x * wpb + wib; sys < a.n_sys; sys += n_waves) {
         wave_sync_lds();
         bool pok = true;
-        if (lane < npl) {
+        if (lane < NPL) {
             const int64_t p = (int64_t)lane * a.n_sys + sys;
-            GradPlanet<double> q;
-            pok = grad_setup(a.P[p], a.K[p], a.e[p], a.w[p], a.M0[p], a.fixed_iter, q);
+            RecG64 q;
+            pok = setup_g64(a.P[p], a.K[p], a.e[p], a.w[p], a.M0[p], q);
             pl[lane] = q;
         }
         const double gam = a.offset ? a.offset[sys] : 0.0;
@@ -103,61 +131,85 @@ __global__ void __launch_bounds__(256) k_gn64(DenseArgs a, double *jtwr, double 
         bool bad_obs = false;
         for (int ch = 0; ch < n_chunks; ++ch) {
             const int64_t k = (int64_t)ch * 64 + lane;
-            if (k < a.n_obs) {
-                const double t = a.t[k], vo = a.v[k], sg = a.sigma[k];
-                const double var = sg * sg + jit * jit;
-                bool ook = isfinite(t) && isfinite(vo) && isfinite(sg) && sg >= 0.0 && var > 0.0;
-                const double sw = ook ? sqrt(1.0 / var) : 0.0;   // sqrt(w) = 1 / sqrt(sigma^2 + s^2)
-                const double tt = t - a.t0;
-                double model = 0.0;
-                for (int j = 0; j < npl; ++j) {
-                    double d[5];
-                    model += grad_eval(pl[j], tt, a.max_iter, fixed, d);
-#pragma unroll
-                    for (int i = 0; i < 5; ++i) row[5 * j + i] = sw * d[i];
-                }
-                const double r = (model + gam) - vo;
-                row[np - 1] = sw;
-                row[np] = sw * r;
-                bad_obs = bad_obs || !ook;
-            } else {
-                for (int c = 0; c <= np; ++c) row[c] = 0.0;    // rows past the last observation
+            const bool in = k < a.n_obs;
+            const double t = in ? a.t[k] : a.t0, vo = in ? a.v[k] : 0.0, sg = in ? a.sigma[k] : 1.0;
+            const double var = sg * sg + jit * jit;
+            const bool ook = isfinite(t) && isfinite(vo) && isfinite(sg) && sg >= 0.0 && var > 0.0;
+            const bool use = in && ook;
+            bad_obs = bad_obs || (in && !ook);
+            const double sw = use ? sqrt(1.0 / var) : 0.0;   // sqrt(w) = 1 / sqrt(sigma^2 + s^2)
+            const double tt[1] = {use ? t - a.t0 : 0.0};     // rows past the last observation stay finite
+            double model = 0.0;
+#pragma nounroll
+            for (int j = 0; j < NPL; ++j) {
+                const RecG64 &p = pl[j];
+                Root64 r[1];
+                double q[1], x[3];
+                roots_g64<ROOT, 1>(p, tt, fixed, a.max_iter, kep_start_tab, knots, r, q);
+                const double dvdK = dvdk_g64(p, r[0]);
+                terms_g64(p, r[0].s, r[0].c, r[0].rD, x);
+                const double swK = sw * p.K;
+                model += p.K * dvdK;
+                double *cj = col + 5 * j * kGn64Col;
+                cj[0 * kGn64Col] = swK * x[0] * (kTwoPi * q[0] * (p.ph.rP == p.ph.rP ? p.ph.rP : 1.0 / p.ph.P));
+                cj[1 * kGn64Col] = sw * dvdK;
+                cj[2 * kGn64Col] = swK * x[1];
+                cj[3 * kGn64Col] = -swK * x[2];
+                cj[4 * kGn64Col] = -swK * x[0];
             }
+            col[(NP - 1) * kGn64Col] = sw;
+            col[NP * kGn64Col] = use ? sw * ((model + gam) - vo) : 0.0;
             wave_sync_lds();
-            // Gram matrix of the 64 rows: A operand lane l = row (4s + l/16),
-            // column (16 bi + l%16); the B operand reads the same pattern for bj.
-            const double *src = T + (lane >> 4) * STRIDE + (lane & 15);
-#pragma unroll 4
-            for (int s = 0; s < 16; ++s) {
-                double av[NB];
 #pragma unroll
-                for (int b = 0; b < NB; ++b) av[b] = src[4 * s * STRIDE + 16 * b];
-                int p = 0;
+            for (int s2 = 0; s2 < 8; ++s2) {
+                double2 av[NOP];
 #pragma unroll
-                for (int bi = 0; bi < NB; ++bi) {
+                for (int b = 0; b < NOP; ++b) av[b] = *reinterpret_cast<const double2 *>(src[b] + 2 * s2);
 #pragma unroll
-                    for (int bj = bi; bj < NB; ++bj) {
-                        acc[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[bi], av[bj], acc[p], 0, 0, 0);
-                        ++p;
+                for (int u = 0; u < 2; ++u) {
+                    double op[NOP];
+#pragma unroll
+                    for (int b = 0; b < NOP; ++b) op[b] = u == 0 ? av[b].x : av[b].y;
+                    if constexpr (TWO) {
+                        acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(op[0], op[1], acc[0], 0, 0, 0);
+                        acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(op[2], op[2], acc[1], 0, 0, 0);
+                    } else {
+                        int p = 0;
+#pragma unroll
+                        for (int bi = 0; bi < NB; ++bi) {
+#pragma unroll
+                            for (int bj = bi; bj < NB; ++bj) {
+                                acc[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(op[bi], op[bj], acc[p], 0, 0, 0);
+                                ++p;
+                            }
+                        }
                     }
                 }
             }
             wave_sync_lds();
         }
         ok = ok && !__any(bad_obs);
-
-        // lane l holds entry (16 bi + l/16 + 4 q, 16 bj + l%16) of block (bi, bj) in acc[.][q]
-        // (the binary64 16x16x4 product interleaves its output rows by four)
-        int p = 0;
 #pragma unroll
-        for (int bi = 0; bi < NB; ++bi) {
+        for (int q = 0; q < 4; ++q) {
+            const int i = (lane >> 4) + 4 * q;
+            if constexpr (TWO) {
+                // X+Y by X+Z, then Y+Z squared (as k_gn_obs)
+                const int c = li < GX ? li : li + 8;
+                if (i < GX + 8 && li < GX + 8 && !(i < GX && c < GX && i > c))
+                    gn_store(a, jtwr, jtwj, sys, NP, i < c ? i : c, i < c ? c : i, ok ? acc[0][q] : nan);
+                const int p2 = GX + i, c2 = GX + li;
+                if (p2 <= c2 && !(p2 < GX + 8 && c2 >= GX + 8))
+                    gn_store(a, jtwr, jtwj, sys, NP, p2, c2, ok ? acc[1][q] : nan);
+            } else {
+                int p = 0;
 #pragma unroll
-            for (int bj = bi; bj < NB; ++bj) {
+                for (int bi = 0; bi < NB; ++bi) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    gn_store(a, jtwr, jtwj, sys, np, 16 * bi + (lane >> 4) + 4 * q, 16 * bj + (lane & 15),
-                             ok ? acc[p][q] : nan);
-                ++p;
+                    for (int bj = bi; bj < NB; ++bj) {
+                        gn_store(a, jtwr, jtwj, sys, NP, 16 * bi + i, 16 * bj + li, ok ? acc[p][q] : nan);
+                        ++p;
+                    }
+                }
             }
         }
     }
@@ -467,18 +519,17 @@ hipError_t launch_gn_mixed(DenseArgs a, double *jtwr, double *jtwj, LaunchShape 
     }
 }
 
-template <class KernelFn>
-hipError_t launch_gn_k(KernelFn kern, size_t per_wave, DenseArgs a, double *jtwr, double *jtwj, LaunchShape shape,
-                       hipStream_t st)
+template <bool ROOT, int NPL>
+hipError_t launch_gn64_t(DenseArgs a, double *jtwr, double *jtwj, LaunchShape shape, hipStream_t st)
 {
-    int wpb = shape.block > 0 ? shape.block / 64 : (int)((64 * 1024) / per_wave);
-    wpb = wpb < 1 ? 1 : (wpb > 4 ? 4 : wpb);
-    if ((size_t)wpb * per_wave > 64 * 1024) return hipErrorInvalidValue;
-    const size_t lds = (size_t)wpb * per_wave;
+    // four wavefronts a block while their tiles and the knots leave three blocks a
+    // CU its 160 KiB (up to four planets), else two
+    const size_t per_wave = gn64_lds_per_wave<NPL>(), knots = ROOT ? kSc64Bytes : 0;
+    const int wpb = shape.block > 0 ? shape.block / 64 : (4 * per_wave + knots <= 53 * 1024 ? 4 : 2);
+    const size_t lds = (size_t)wpb * per_wave + knots;
+    void (*kern)(DenseArgs, double *, double *) = k_gn64<ROOT, NPL>;
     int per_cu = shape.blocks_per_cu;
-    if (per_cu <= 0) {
-        per_cu = cached_occupancy((const void *)kern, wpb * 64, lds);
-    }
+    if (per_cu <= 0) per_cu = cached_occupancy((const void *)kern, wpb * 64, lds);
     int64_t grid = (a.n_sys + wpb - 1) / wpb;
     const int64_t cap = (int64_t)device_cu_count() * per_cu;
     if (grid > cap) grid = cap;
@@ -487,10 +538,31 @@ hipError_t launch_gn_k(KernelFn kern, size_t per_wave, DenseArgs a, double *jtwr
     return hipGetLastError();
 }
 
-template <int NB>
-hipError_t launch_gn64_t(DenseArgs a, double *jtwr, double *jtwj, LaunchShape shape, hipStream_t st)
+template <int NPL>
+hipError_t launch_gn64_npl(DenseArgs a, double *jtwr, double *jtwj, LaunchShape shape, hipStream_t st)
 {
-    return launch_gn_k(k_gn64<NB>, gn64_lds_per_wave<NB>(), a, jtwr, jtwj, shape, st);
+    // a caller's block size whose row-major binary64 tiles (the layout before the
+    // live-column one) did not fit 64 KiB was refused, and stays so
+    constexpr int nb = (5 * NPL + 2 + 15) / 16;
+    constexpr size_t refused_per_wave = ((size_t)64 * (16 * nb + 1) * sizeof(double) + 8 * 64 + 15) & ~(size_t)15;
+    if (shape.block > 0 && (size_t)(shape.block / 64) * refused_per_wave > 64 * 1024) return hipErrorInvalidValue;
+    return a.fixed_iter == 0 ? launch_gn64_t<true, NPL>(a, jtwr, jtwj, shape, st)
+                             : launch_gn64_t<false, NPL>(a, jtwr, jtwj, shape, st);
+}
+
+hipError_t launch_gn64(DenseArgs a, double *jtwr, double *jtwj, LaunchShape shape, hipStream_t st)
+{
+    switch (a.n_pl) {
+        case 1: return launch_gn64_npl<1>(a, jtwr, jtwj, shape, st);
+        case 2: return launch_gn64_npl<2>(a, jtwr, jtwj, shape, st);
+        case 3: return launch_gn64_npl<3>(a, jtwr, jtwj, shape, st);
+        case 4: return launch_gn64_npl<4>(a, jtwr, jtwj, shape, st);
+        case 5: return launch_gn64_npl<5>(a, jtwr, jtwj, shape, st);
+        case 6: return launch_gn64_npl<6>(a, jtwr, jtwj, shape, st);
+        case 7: return launch_gn64_npl<7>(a, jtwr, jtwj, shape, st);
+        case 8: return launch_gn64_npl<8>(a, jtwr, jtwj, shape, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace
@@ -499,11 +571,7 @@ hipError_t launch_gn(DenseArgs a, double *jtwr, double *jtwj, Prec prec, LaunchS
 {
     if (a.n_sys <= 0) return hipSuccess;
     if (prec == Prec::Mixed) return launch_gn_mixed(a, jtwr, jtwj, shape, st);
-    const int ncol = 5 * a.n_pl + 2;   // parameters, offset, residual
-    if (ncol <= 16) return launch_gn64_t<1>(a, jtwr, jtwj, shape, st);
-    if (ncol <= 32) return launch_gn64_t<2>(a, jtwr, jtwj, shape, st);
-    if (ncol <= 48) return launch_gn64_t<3>(a, jtwr, jtwj, shape, st);
-    return hipErrorInvalidValue;
+    return launch_gn64(a, jtwr, jtwj, shape, st);
 }
 
 }  // namespace kep

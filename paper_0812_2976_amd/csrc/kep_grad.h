@@ -17,27 +17,6 @@ namespace kep {
 // dE/dM = 1/(1 - e cos E) and dE/de = sin E/(1 - e cos E), in the true-anomaly forms
 //   df/dM = b/D^2,  df/de = sin E (2 - e cos E - e^2)/(b D^2),  D = 1 - e cos E,
 // so no iteration is differentiated.
-template <class T> struct GradPlanet;
-
-template <> struct GradPlanet<double> {
-    double P, rP, M0, e, b, K, cw, sw;
-};
-
-__device__ __forceinline__ bool grad_setup(double P, double K, double e, double w, double M0, int,
-                                           GradPlanet<double> &g)
-{
-    bool ok = planet_ok(P, K, e, w, M0);
-    if (!ok) { P = 1.0; K = 0.0; e = 0.0; w = 0.0; M0 = 0.0; }
-    g.P = P;
-    g.rP = 1.0 / P;
-    g.M0 = M0;
-    g.e = e;
-    g.b = sqrt((1.0 - e) * (1.0 + e));
-    g.K = K;
-    sincos(w, &g.sw, &g.cw);
-    return ok;
-}
-
 // ---------------------------------------------------------------------------
 // Mixed-precision adjoint with a binary64 correction of the root.  The binary32
 // iteration leaves E with an error of a few 1e-7 rad / (1 - e cos E) (the
@@ -355,38 +334,5 @@ __device__ __forceinline__ float rows_reduce_scatter(float (&x)[R])
     for (int o = 32 / R; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
-
-// binary64 plain path: velocity of one planet and its five partial derivatives
-// d[0..4] = dv/d(P, K, e, omega, M0) at tt = t - t0.
-__device__ __forceinline__ double grad_eval(const GradPlanet<double> &g, double tt, int max_iter, int fixed,
-                                            double (&d)[5])
-{
-    double q = tt / g.P;
-    double phi = q - floor(q);
-    double M = fma(kTwoPi, phi, g.M0);
-    M = M - kTwoPi * floor(M * kInvTwoPi);
-    double E = kepler64(M, g.e, M < kPi ? 1.0 : -1.0, fixed, max_iter);
-    double s, c;
-    sincos(E, &s, &c);
-    double D = 1.0 - g.e * c;
-    double cf = (c - g.e) / D;
-    double sf = g.b * s / D;
-    double cwf = g.cw * cf - g.sw * sf;
-    double swf = g.sw * cf + g.cw * sf;
-    double dvdK = cwf + g.e * g.cw;
-    double dfdM = g.b / (D * D);
-    double dfde = s * (2.0 - g.e * c - g.e * g.e) / (g.b * D * D);
-    double dvdM0 = -g.K * swf * dfdM;
-    d[0] = dvdM0 * (-kTwoPi * q / g.P);
-    d[1] = dvdK;
-    d[2] = g.K * g.cw - g.K * swf * dfde;
-    d[3] = -g.K * (swf + g.e * g.sw);
-    d[4] = dvdM0;
-    return g.K * dvdK;
-}
-
-// NLL = true: the Gaussian likelihood with jitter, -2 ln L = chi2 +
-// sum_k ln(sigma_k^2 + s^2) (constant dropped), and one more gradient row,
-// d/ds = 2 s (sum_k w_k - sum_k w_k^2 r_k^2).
 
 }  // namespace kep

@@ -110,7 +110,8 @@ struct LaunchShape {
 hipError_t launch_kepler_solve(const double *M, const double *e, double *E, int64_t n, Prec prec,
                                int fixed_iter, int max_iter, LaunchShape shape, hipStream_t st);
 hipError_t launch_dense(DenseArgs a, Prec prec, bool model, LaunchShape shape, hipStream_t st);
-hipError_t launch_dense_grad(DenseArgs a, Prec prec, bool nll, LaunchShape shape, hipStream_t st);
+// the binary64 gradient and likelihood (kep_grad64.hip)
+hipError_t launch_grad64(DenseArgs a, bool nll, LaunchShape shape, hipStream_t st);
 // the mixed-precision adjoint (lanes over observations, binary64 correction of E and v)
 hipError_t launch_grad_mixed(DenseArgs a, bool nll, LaunchShape shape, hipStream_t st);
 hipError_t launch_planet_velocities(DenseArgs a, LaunchShape shape, hipStream_t st);
@@ -121,10 +122,10 @@ int ragged_max_grid(LaunchShape shape, int sb, int gmax);
 // (into the static scratch array), then runs the persistent kernel; a.order
 // and a.queue are set here.  a.sb and a.gmax must be set.  No allocation.
 hipError_t launch_ragged_static(RaggedArgs a, LaunchShape shape, hipStream_t st);
-// Plain binary64 ragged chi-square (kep_ragged64.hip): one wavefront per system, grid-stride over the
+// Plain binary64 ragged chi-square (kep_ragged64.hip): one wavefront per few systems, grid-stride over the
 // work order (a.order, or the systems in order when null); checks every system's offsets itself.
 hipError_t launch_ragged64(RaggedArgs a, LaunchShape shape, hipStream_t st);
-int ragged64_grid(LaunchShape shape, int64_t n_sys);   // the blocks launch_ragged64 launches
+int ragged64_grid(LaunchShape shape, int64_t n_sys, int fixed_iter);   // the blocks launch_ragged64 launches
 bool ragged_shape_fits(int block, int sb);   // LDS of the persistent kernel (slices + table) within 64 KiB
 hipError_t launch_astro(AstroArgs a, Prec prec, bool model, LaunchShape shape, hipStream_t st);
 // Gauss-Newton products: chi2 into a.out, J^T W r [np][n_sys], packed J^T W J
@@ -140,6 +141,26 @@ hipError_t launch_demc_advance(uint64_t *gen, uint64_t inc, hipStream_t st);
 // one fused half-step (propose, chi-square, accept) of half h
 hipError_t launch_demc_half(DemcArgs m, DenseArgs base, Prec prec, int h, LaunchShape shape, hipStream_t st);
 int device_cu_count();
+
+// Systems per setup batch of a wavefront for n_sys systems over `waves` resident
+// wavefronts, at most `cap`: as many rounds of batches as the cap asks for, and
+// the smallest batch that still takes no more rounds, so that the last round is
+// as full as the others.
+inline int systems_per_batch(int64_t n_sys, int64_t waves, int64_t cap)
+{
+    if (waves < 1) waves = 1;
+    const int64_t rounds = (n_sys + waves * cap - 1) / (waves * cap);
+    const int64_t per = waves * (rounds < 1 ? 1 : rounds);
+    const int64_t sb = (n_sys + per - 1) / per;
+    return (int)(sb < 1 ? 1 : (sb > cap ? cap : sb));
+}
+
+// LDS of a block of which `blocks` share a CU: its 160 KiB are handed out in
+// pieces of 1,280 bytes (five blocks of 32,768 bytes do not fit, five of 32,000
+// do: the astrometric kernel at 200,000 x 2 x 128, 237 against 214 us).
+constexpr int64_t kLdsBytes = 160 * 1024, kLdsPiece = 1280;
+constexpr int64_t lds_budget(int blocks) { return kLdsBytes / blocks / kLdsPiece * kLdsPiece; }
+
 // blocks of `kern` per CU at this block size and dynamic LDS (cached per device)
 int cached_occupancy(const void *kern, int block, size_t lds);
 

@@ -346,67 +346,6 @@ __global__ void __launch_bounds__(256) k_kepler(const double *__restrict__ Mv, c
     }
 }
 
-// ------------------------------------------------------------------ gradient
-// Plain binary64 chi-square and gradient with one lane per system (the
-// adjoint needs 5 n_pl + 1 running sums per system; the lane that owns the
-// system keeps them).  Observations are uniform across the wave and arrive
-// through scalar loads.  The mixed-precision adjoint is in kep_adjoint.hip.
-template <int NPL, bool NLL>
-__global__ void __launch_bounds__(256) k_grad_f64(DenseArgs a)
-{
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const bool has_jit = a.jitter != nullptr;
-    const int fixed = fixed64(a.fixed_iter);
-    for (int64_t sys = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; sys < a.n_sys; sys += stride) {
-        GradPlanet<double> pl[NPL];
-        bool ok = isfinite(a.t0);
-#pragma unroll
-        for (int j = 0; j < NPL; ++j) {
-            const int64_t p = (int64_t)j * a.n_sys + sys;
-            ok = grad_setup(a.P[p], a.K[p], a.e[p], a.w[p], a.M0[p], a.fixed_iter, pl[j]) && ok;
-        }
-        const double gam = a.offset ? a.offset[sys] : 0.0;
-        const double jit = a.jitter ? a.jitter[sys] : 0.0;
-        if (a.offset) ok = ok && isfinite(gam);
-        if (has_jit) ok = ok && isfinite(jit) && jit >= 0.0;
-        double chi = 0.0, gacc[5 * NPL + 1];
-        double sum_lv = 0.0, sum_w = 0.0, sum_wr2 = 0.0;
-#pragma unroll
-        for (int i = 0; i < 5 * NPL + 1; ++i) gacc[i] = 0.0;
-        for (int64_t k = 0; k < a.n_obs; ++k) {
-            const double t = a.t[k], vo = a.v[k], sg = a.sigma[k];
-            ok = ok && isfinite(t) && isfinite(vo) && isfinite(sg) && sg >= 0.0;
-            const double tt = t - a.t0;
-            double d[NPL][5];
-            double m = 0.0;
-#pragma unroll
-            for (int j = 0; j < NPL; ++j) m += grad_eval(pl[j], tt, a.max_iter, fixed, d[j]);
-            const double r = m + gam - vo;
-            const double var = sg * sg + jit * jit;
-            ok = ok && var > 0.0;
-            const double w = 1.0 / var;
-            chi = fma(w * r, r, chi);
-            if (NLL) {
-                sum_lv += log(var);
-                sum_w += w;
-                sum_wr2 = fma(w * r, w * r, sum_wr2);
-            }
-            const double c2 = 2.0 * w * r;
-#pragma unroll
-            for (int j = 0; j < NPL; ++j) {
-#pragma unroll
-                for (int i = 0; i < 5; ++i) gacc[5 * j + i] = fma(c2, d[j][i], gacc[5 * j + i]);
-            }
-            gacc[5 * NPL] += c2;
-        }
-        const double nan = __builtin_nan("");
-        a.out[sys] = ok ? chi + sum_lv : nan;
-#pragma unroll
-        for (int i = 0; i < 5 * NPL + 1; ++i) a.grad[(int64_t)i * a.n_sys + sys] = ok ? gacc[i] : nan;
-        if (NLL) a.grad[(int64_t)(5 * NPL + 1) * a.n_sys + sys] = ok ? 2.0 * jit * (sum_w - sum_wr2) : nan;
-    }
-}
-
 // ------------------------------------------------------------------ ragged
 // Persistent kernel over CSR systems.  Work items are runs of `sb` systems of
 // the plan's work order (decreasing work, grouped by planet count within
@@ -974,10 +913,9 @@ static hipError_t launch_dense_t(DenseArgs a, LaunchShape shape, hipStream_t st)
                      : rec_bytes * (size_t)sb;
     };
     // systems per setup batch: at most kMaxSB and at most 48 KiB of LDS per block
-    // (with the table, 32 KiB: five blocks of four wavefronts share a CU's 160 KiB;
-    // with the knots too, 40 KiB and four blocks)
-    const int64_t budget = table ? (int64_t)((Pol::kTables == 2 ? 40 : 32) * 1024) -
-                                       (int64_t)dense_table_bytes<Pol>() - 16
+    // (with the table, five blocks of four wavefronts share a CU's LDS; with the
+    // knots too, four)
+    const int64_t budget = table ? lds_budget(Pol::kTables == 2 ? 4 : 5) - (int64_t)dense_table_bytes<Pol>() - 16
                                  : (int64_t)(48 * 1024);
     int64_t sb_cap = budget / (int64_t)rec_bytes;
     sb_cap = sb_cap < 1 ? 1 : (sb_cap > kMaxSB ? kMaxSB : sb_cap);
@@ -1063,40 +1001,6 @@ hipError_t launch_chisq_from_velocities(DenseArgs a, LaunchShape shape, hipStrea
 }  // namespace kep
 
 namespace kep {
-
-static int grad_grid(int64_t n_sys, int block, int per_cu)
-{
-    int64_t need = (n_sys + block - 1) / block;
-    int64_t cap = (int64_t)device_cu_count() * (per_cu > 0 ? per_cu : 8);
-    return (int)(need < cap ? (need > 0 ? need : 1) : cap);
-}
-
-hipError_t launch_dense_grad(DenseArgs a, Prec prec, bool nll, LaunchShape shape, hipStream_t st)
-{
-    if (a.n_sys <= 0) return hipSuccess;
-    if (prec == Prec::Mixed) return launch_grad_mixed(a, nll, shape, st);
-    const int block = shape.block > 0 ? shape.block : 256;
-    const int grid = grad_grid(a.n_sys, block, shape.blocks_per_cu);
-#define KEP_GRAD_LAUNCH(N, L) hipLaunchKernelGGL((k_grad_f64<N, L>), dim3(grid), dim3(block), 0, st, a);
-#define KEP_GRAD_CASE(N)                                                                     \
-    case N:                                                                                  \
-        if (nll) { KEP_GRAD_LAUNCH(N, true) } else { KEP_GRAD_LAUNCH(N, false) }              \
-        break;
-    switch (a.n_pl) {
-        KEP_GRAD_CASE(1)
-        KEP_GRAD_CASE(2)
-        KEP_GRAD_CASE(3)
-        KEP_GRAD_CASE(4)
-        KEP_GRAD_CASE(5)
-        KEP_GRAD_CASE(6)
-        KEP_GRAD_CASE(7)
-        KEP_GRAD_CASE(8)
-        default: return hipErrorInvalidValue;
-    }
-#undef KEP_GRAD_CASE
-#undef KEP_GRAD_LAUNCH
-    return hipGetLastError();
-}
 
 static size_t ragged_lds(int block, int sb)
 {

@@ -167,9 +167,8 @@ __device__ __forceinline__ Phase64c make_phase64c(double P, double M0)
 // where 1/P overflows), q less its nearest integer exactly, 2 pi times it plus
 // M0 in one fused multiply-add, reduced once more with 2 pi in two parts.
 // Each rounding is at a magnitude of at most 2 pi (4 pi before centring).
-__device__ __forceinline__ double mean_anomaly64c(double tt, const Phase64c &p)
+__device__ __forceinline__ double mean_anomaly64c(double tt, const Phase64c &p, double &q)
 {
-    double q;
     if (p.rP == p.rP) {
         const double q0 = tt * p.rP;
         q = fma(fma(-q0, p.P, tt), p.rP, q0);
@@ -239,7 +238,8 @@ struct Pol64R {
         float M32[NCH], E32[NCH], sv[NCH], omc[NCH];
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-            M[c] = mean_anomaly64c(o[c].tt, ph);
+            double q;
+            M[c] = mean_anomaly64c(o[c].tt, ph, q);
             M32[c] = (float)M[c];
         }
         PolMixed::solve<NCH, false>(rr.k, uniform_int(rr.niter), false, rr.tp, M32, E32, sv, omc, max_iter, tab);
@@ -264,5 +264,91 @@ struct Pol64R {
     }
     static __device__ __forceinline__ double chi_value(const ChiAcc &x) { return x; }
 };
+
+// ------------------------------------------------------------ derivatives
+// Per-planet record of the binary64 gradient and Gauss-Newton products.
+struct RecG64 {            // 112 bytes
+    Phase64c ph;
+    double e, b, rb, b2, K, cw, sw;   // b = sqrt(1 - e^2), rb = 1/b, b2 = 1 - e^2
+    Ecc32 k;                          // of the binary32 starting solve, as Rec64R
+    TabPlace tp;
+    int16_t niter;
+    int16_t pad;
+};
+
+__device__ __forceinline__ bool setup_g64(double P, double K, double e, double w, double M0, RecG64 &r)
+{
+    const bool ok = planet_ok(P, K, e, w, M0);
+    if (!ok) { P = 1.0; K = 0.0; e = 0.0; w = 0.0; M0 = 0.0; }
+    r.ph = make_phase64c(P, M0);
+    r.e = e;
+    r.b2 = (1.0 - e) * (1.0 + e);
+    r.b = sqrt(r.b2);
+    r.rb = 1.0 / r.b;
+    r.K = K;
+    sincos(w, &r.sw, &r.cw);
+    r.k = make_ecc32(e);
+    r.tp = table_place(e, true);
+    r.niter = (int16_t)sched32(r.k.e);
+    r.pad = 0;
+    return ok;
+}
+
+// sin E, cos E, D = 1 - e cos E and 1/D of NCH observations of one planet (a
+// wave-uniform record), and q = (t - t0)/P.  ROOT: the default step count
+// (tab, knots as in Pol64R); else Danby's plain iteration, `fixed` steps (0: its
+// schedule and convergence test).
+template <bool ROOT, int NCH>
+__device__ __forceinline__ void roots_g64(const RecG64 &rr, const double (&tt)[NCH], int fixed, int max_iter,
+                                          const uint32_t *tab, const double2 *knots, Root64 (&r)[NCH],
+                                          double (&q)[NCH])
+{
+    const Phase64c ph = rr.ph;
+    const double e = rr.e;
+    double M[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) M[c] = mean_anomaly64c(tt[c], ph, q[c]);
+    if constexpr (ROOT) {
+        float M32[NCH], E32[NCH], sv[NCH], omc[NCH];
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) M32[c] = (float)M[c];
+        PolMixed::solve<NCH, false>(rr.k, uniform_int(rr.niter), false, rr.tp, M32, E32, sv, omc, max_iter, tab);
+        const bool far = uniform_int(rr.tp.toff) < 0;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) refine_root64(e, E32[c], M[c], far, knots, r[c]);
+    } else {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            r[c].E = kepler64(M[c], e, M[c] >= 0.0 ? 1.0 : -1.0, fixed, max_iter);
+            sincos(r[c].E, &r[c].s, &r[c].c);
+            r[c].D = 1.0 - e * r[c].c;
+            r[c].rD = 1.0 / r[c].D;
+        }
+    }
+}
+
+// dv/dK = cos(w+f) + e cos w = b (b cos w cos E - sin w sin E)/D: the velocity is
+// K times it (the quotient corrected by its remainder).
+__device__ __forceinline__ double dvdk_g64(const RecG64 &p, const Root64 &r)
+{
+    const double num = p.b * fma(p.b * p.cw, r.c, -(p.sw * r.s));
+    const double v = num * r.rD;
+    return fma(fma(-v, r.D, num), r.rD, v);
+}
+
+// The other terms of planet p's derivatives from sin E, cos E and 1/D, by the
+// implicit-function relations (df/dM = b/D^2, df/de = sin E (D + 1 - e^2)/(b D^2)):
+//   dv/dP = (2 pi K/P) q x[0], dv/de = K x[1], dv/dw = -K x[2], dv/dM0 = -K x[0];
+// x[2] = sin(w+f) + e sin w in the form b (b sin w cos E + cos w sin E)/D, which
+// does not cancel near apoapsis.
+__device__ __forceinline__ void terms_g64(const RecG64 &p, double s, double c, double rD, double (&x)[3])
+{
+    const double bs = p.b * s;
+    const double swf = fma(p.sw, c - p.e, p.cw * bs) * rD;        // sin(w + f)
+    const double t = swf * rD;
+    x[0] = t * (p.b * rD);
+    x[1] = fma(-t, (s * p.rb) * fma(p.b2, rD, 1.0), p.cw);            // rD (D + b2) = 1 + b2 rD
+    x[2] = p.b * rD * fma(p.b * p.sw, c, p.cw * s);
+}
 
 }  // namespace kep
