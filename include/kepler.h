@@ -301,15 +301,15 @@ kep_status rv_chisq_ragged_direct(kep_plan *plan, double *chi2, void *stream);
    capture, tight serving loops, harnesses that forbid allocation): the
    chi-square of a ragged batch in one call, without a plan.  Allocates
    nothing (no hipMalloc, hipFree or allocating library call) and does not
-   synchronise: two kernels on `stream`.  The first checks each system's
-   offsets on the device and writes the work order (systems by decreasing
+   synchronise: three kernels on `stream`.  The first two check each system's
+   offsets on the device and write the work order (systems by decreasing
    planet count, index order within a count, so results are the same on every
-   call) into a static device work area of the library; the second is the
+   call) into a static device work area of the library; the third is the
    plan's persistent kernel at a fixed launch shape (256-thread blocks or
    opts->block_threads, 16 systems per work item).
    Arguments as kep_plan_ragged plus chi2[n_sys] (caller-owned device array).
    Limit: n_sys <= 2,097,152 (the work area holds a 32-bit order entry per
-   system after 2 KiB of work-queue counters; 8 MiB + 2 KiB per GPU, held
+   system after 74 KiB of counters; 8 MiB + 74 KiB per GPU, held
    until the process ends); larger
    batches return KEP_ERR_SHAPE.  Offsets are not read on the host: a system
    whose offsets fall outside [0, n_obs_total] / [0, n_pl_total], decrease, or

@@ -824,11 +824,11 @@ kep_status rv_chisq_ragged_static(const kep_obs_csr *obs, const kep_params_csr *
     }
     // the launch shape the autotuner picks for the c3-like batches it has seen:
     // 16 systems per work item, observation groups of up to four 64-lane chunks
+    // (small batches: launch_ragged_static)
     a.sb = 16;
     a.gmax = 4;
-    kep::LaunchShape shape = o.shape;
-    if (shape.block == 0) shape.block = 256;
-    if (!kep::ragged_shape_fits(shape.block, a.sb)) return fail(KEP_ERR_ARG, "%s: block_threads too large", fn);
+    const kep::LaunchShape shape = o.shape;
+    if (!kep::ragged_shape_fits(shape.block > 0 ? shape.block : 256, a.sb)) return fail(KEP_ERR_ARG, "%s: block_threads too large", fn);
     return launch_status(kep::launch_ragged_static(a, shape, (hipStream_t)stream), fn);
 }
 

@@ -92,12 +92,15 @@ constexpr int kMaxSB = 32;
 constexpr int kMaxPl = 8;
 
 // Allocation-free ragged path: a static device array holds the queue counters
-// (the first kStaticQueueBytes) and the int32 work order of at most
-// kStaticMaxSys systems.
+// (the first kStaticQueueBytes), the per-tile counts of the ordering kernels and
+// the int32 work order of at most kStaticMaxSys systems.
 constexpr int64_t kStaticMaxSys = 1 << 21;
 constexpr size_t kStaticQueueBytes = 2048;
 static_assert(sizeof(unsigned int) * kQueueWords <= kStaticQueueBytes, "queue counters exceed their area");
-constexpr size_t kStaticScratchBytes = kStaticQueueBytes + sizeof(int32_t) * (size_t)kStaticMaxSys;
+constexpr int kStaticTile = 1024;                                   // systems per block of the ordering kernels
+constexpr int kStaticMaxTiles = (int)(kStaticMaxSys / kStaticTile);
+constexpr size_t kStaticCountBytes = sizeof(int) * (size_t)(kMaxPl + 1) * kStaticMaxTiles;
+constexpr size_t kStaticScratchBytes = kStaticQueueBytes + kStaticCountBytes + sizeof(int32_t) * (size_t)kStaticMaxSys;
 
 enum class Prec { F64 = 0, Mixed = 1 };
 

@@ -430,6 +430,8 @@ __device__ __forceinline__ float ragged_vel_lane(const RecMixed &r, double tt, i
 // (code, system) pairs [sb][2], where code is the planet count, negative for
 // an invalid system; per-planet domain flags [sb][kMaxPl]; prefix sums of the
 // tail lengths [sb + 1]; bad-data flags [sb].
+// With COOP one such slice serves a block, which adds each wavefront's share of
+// the systems' chi-square [sb] after it.
 __host__ __device__ inline size_t ragged_lds_per_wave(int sb)
 {
     const size_t b = (size_t)sb * kMaxPl * sizeof(RecMixed) + (size_t)sb * 2 * sizeof(int64_t) +
@@ -451,25 +453,43 @@ __device__ __forceinline__ int64_t uniform_i64(int64_t x)
 // autotuner picks it.  Five wavefronts per SIMD with two chunks (96 VGPRs, 16
 // bytes of scratch), four with four (128 VGPRs, 68 bytes): at c3 the four-chunk
 // form at four wavefronts runs 3% faster than the two-chunk one at four.
-template <int GMAX>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GMAX == 2 ? 5 : 4))) k_ragged_mixed(RaggedArgs a)
+//
+// COOP: a block takes an item, not a wavefront: its wavefronts build the item's
+// records together, take its units and its tail groups in turn, each keeping its
+// own sums, which are added in wavefront order at the end.  For batches of fewer
+// items than the chip has wavefronts (30,011 systems in items of 16: 1,876
+// items), where one wavefront per item left most of the chip idle for as long as
+// the largest item takes.  The evaluations are the same: units, and groups of 64
+// tail lanes, hold the same observations in either form.
+template <int GMAX, bool COOP>
+__global__ void __launch_bounds__(COOP ? 1024 : 256) __attribute__((amdgpu_waves_per_eu(GMAX == 2 ? 5 : 4)))
+k_ragged_mixed(RaggedArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = __lane_id();
     const int wib = uniform_int(threadIdx.x >> 6);
+    const int wpb = blockDim.x >> 6;
     const int sb = a.sb;
-    unsigned char *mine = smem + (size_t)wib * ragged_lds_per_wave(sb);
+    // the threads that share an item: tid of nthr
+    const int tid = COOP ? (int)threadIdx.x : lane, nthr = COOP ? (int)blockDim.x : 64;
+    auto sync_item = [] {
+        if constexpr (COOP) __syncthreads();
+        else wave_sync_lds();
+    };
+    unsigned char *mine = smem + (COOP ? 0 : (size_t)wib * ragged_lds_per_wave(sb));
     RecMixed *recs = reinterpret_cast<RecMixed *>(mine);
     int64_t *pofs = reinterpret_cast<int64_t *>(recs + sb * kMaxPl);
     int64_t *tail0 = pofs + sb;
-    double *acc = reinterpret_cast<double *>(tail0 + sb);
-    int64_t *obs0 = reinterpret_cast<int64_t *>(acc + sb);
+    double *acc0 = reinterpret_cast<double *>(tail0 + sb);
+    int64_t *obs0 = reinterpret_cast<int64_t *>(acc0 + sb);
     int64_t *nfl = obs0 + sb;
     double *gj = reinterpret_cast<double *>(nfl + sb);
     int *meta = reinterpret_cast<int *>(gj + 2 * sb);
     int *okpl = meta + 2 * sb;
     int *tpre = okpl + sb * kMaxPl;
     int *bad = tpre + sb + 1;
+    // this wavefront's sums: the slice's own, or one of the block's wavefronts'
+    double *acc = COOP ? reinterpret_cast<double *>(smem + ragged_lds_per_wave(sb)) + wib * sb : acc0;
     const bool has_jit = a.jitter != nullptr;
     __shared__ uint32_t tab[kTabWords];    // Kepler starting values
     __shared__ unsigned int drained;       // bit q: a wave of this block found queue q drained
@@ -487,9 +507,25 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GMAX =
     // (c3: 0.611 -> 0.599 ms together with the block-level exit count below).
     const int home = (int)(blockIdx.x % kRaggedQueues);
     int tried = 0;
+    bool first_item = true;
+    __shared__ int64_t taken;              // COOP: the block's item
     for (;;) {
         int64_t item = -1;
-        while (tried < kRaggedQueues) {               // uniform: every lane takes part in the shuffle
+        if constexpr (COOP) {
+            // block b's first item is b; items past the grid come from one counter
+            // (a probe of eight drained queues, one after another, was 8 us of a
+            // launch of 28)
+            if (!first_item && (int64_t)gridDim.x >= a.n_items) break;
+            __syncthreads();                          // every wavefront is done with the previous item
+            if (threadIdx.x == 0)
+                taken = first_item ? (int64_t)blockIdx.x
+                                   : (int64_t)gridDim.x + (int64_t)atomicAdd(a.queue, 1u);
+            first_item = false;
+            __syncthreads();
+            item = uniform_i64(taken);
+            if (item >= a.n_items) item = -1;
+        }
+        while (!COOP && tried < kRaggedQueues) {      // uniform: every lane takes part in the shuffle
             const int q = (home + tried) % kRaggedQueues;
             // a relaxed read: a mark not yet seen costs one more probe, nothing else
             const unsigned int seen = __hip_atomic_load(&drained, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -513,9 +549,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GMAX =
         const int nb = (int)min((int64_t)sb, a.n_sys - i0);
         wave_sync_lds();
         int rem = 0;
+        // (COOP: every wavefront reads them for the prefix sums, the first one writes)
         if (lane < nb) {
             const int32_t code = a.order[i0 + lane];
-            if (code >= 0) {
+            if (COOP && wib != 0) {
+                if (code >= 0) rem = (int)((a.obs_off[code + 1] - a.obs_off[code]) & 63);
+            } else if (code >= 0) {
                 const int64_t sys = code;
                 const int64_t p0 = a.pl_off[sys];
                 const int64_t o0 = a.obs_off[sys], n = a.obs_off[sys + 1] - o0;
@@ -543,7 +582,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GMAX =
                 nfl[lane] = 0;
             }
             acc[lane] = 0.0;
-            bad[lane] = 0;
+            if (!COOP || wib == 0) bad[lane] = 0;
         }
         // prefix sums of the tail lengths over the item's systems
         int incl = rem;
@@ -551,13 +590,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GMAX =
             const int u = __shfl_up(incl, d, 64);
             if (lane >= d) incl += u;
         }
-        if (lane < nb) tpre[lane + 1] = incl;
-        if (lane == 0) tpre[0] = 0;
+        if (!COOP || wib == 0) {
+            if (lane < nb) tpre[lane + 1] = incl;
+            if (lane == 0) tpre[0] = 0;
+        }
         const int ntail = uniform_int(__shfl(incl, nb - 1, 64));
-        wave_sync_lds();
+        sync_item();
         DenseArgs dummy;
         dummy.fixed_iter = a.fixed_iter;
-        for (int q = lane; q < nb * kMaxPl; q += 64) {
+        for (int q = tid; q < nb * kMaxPl; q += nthr) {
             const int s = q / kMaxPl, j = q - s * kMaxPl;
             if (j < meta[2 * s]) {
                 const int64_t p = pofs[s] + j;
@@ -566,8 +607,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GMAX =
                 recs[q] = r;
             }
         }
-        wave_sync_lds();
-        if (lane < nb) {
+        sync_item();
+        if (lane < nb && (!COOP || wib == 0)) {
             const int npl = meta[2 * lane];
             bool ok = isfinite(a.t0) && npl >= 1 && npl <= kMaxPl;
             for (int j = 0; j < kMaxPl; ++j)
@@ -577,14 +618,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GMAX =
             if (a.jitter) ok = ok && isfinite(sj) && sj >= 0.0;
             meta[2 * lane] = ok ? npl : -npl;
         }
-        wave_sync_lds();
+        sync_item();
         // whole groups of 64 observations, one system at a time, in units of up to
         // GMAX groups.  Each unit's observations are loaded when it starts: the
         // other resident wavefronts cover the wait, and loading the next unit's
         // ahead (registers for two units) cost a wavefront per SIMD, 3% at c3.
         {
             auto has_units = [&](int q) { return uniform_int(meta[2 * q]) > 0 && uniform_i64(nfl[q]) > 0; };
-            int us = 0;
+            int us = 0, turn = 0;                        // COOP: units go to the wavefronts in turn
             while (us < nb && !has_units(us)) ++us;
             int64_t ug = 0;
             RawObs<GMAX> cur;
@@ -600,6 +641,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GMAX =
                     while (ns < nb && !has_units(ns)) ++ns;
                     ng = 0;
                 }
+                const bool my_turn = !COOP || turn == wib;
+                if (COOP && ++turn == wpb) turn = 0;
+                if (!my_turn && ns == us) {
+                    ug = ng;
+                    continue;
+                }
+                if (my_turn) {
                 load_unit<GMAX>(a, uniform_i64(obs0[us]) + ug, nf - ug, cur);
                 const int64_t left = nf - ug;
                 const int code = uniform_int(meta[2 * us]);
@@ -610,12 +658,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GMAX =
                     ragged_unit<2, GMAX>(a, rs, code, cur, left, gam, jit, has_jit, chi, bad_obs, tab);
                 else if (left <= 192) ragged_unit<3, GMAX>(a, rs, code, cur, left, gam, jit, has_jit, chi, bad_obs, tab);
                 else ragged_unit<GMAX, GMAX>(a, rs, code, cur, left, gam, jit, has_jit, chi, bad_obs, tab);
+                }
                 if (ns != us) {
                     const double tot = wave_sum(PolMixed::chi_value(chi));
                     const bool b = __any(bad_obs);
                     if (lane == 0) {
                         acc[us] = tot;
-                        bad[us] = b ? 1 : 0;
+                        if (b) bad[us] = 1;             // every writer stores the same value
                     }
                     PolMixed::chi_init(chi);
                     bad_obs = false;
@@ -646,18 +695,19 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GMAX =
                     sg = __builtin_nontemporal_load(a.sigma + k);
                 }
             };
-            bool in = lane < ntail;
-            int pp = in ? lane : ntail - 1;
+            const int first = COOP ? 64 * wib : 0, step = COOP ? 64 * wpb : 64;
+            bool in = first + lane < ntail;
+            int pp = in ? first + lane : ntail - 1;
             seek(pp);
             double t, v, sg;
             fetch(pp, in, t, v, sg);
-            for (int c0 = 0; c0 < ntail; c0 += 64) {
+            for (int c0 = first; c0 < ntail; c0 += step) {
                 const int sc = s;
                 const bool inc = in;
                 const double tc = t, vc = v, sgc = sg;
-                if (c0 + 64 < ntail) {                  // next group: cursor and loads
-                    in = c0 + 64 + lane < ntail;
-                    pp = in ? c0 + 64 + lane : ntail - 1;
+                if (c0 + step < ntail) {                // next group: cursor and loads
+                    in = c0 + step + lane < ntail;
+                    pp = in ? c0 + step + lane : ntail - 1;
                     seek(pp);
                     fetch(pp, in, t, v, sg);
                 }
@@ -698,9 +748,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GMAX =
                 wave_sync_lds();
             }
         }
-        if (lane < nb) {
+        if constexpr (COOP) __syncthreads();
+        if (lane < nb && (!COOP || wib == 0)) {
             const int code = meta[2 * lane];
-            a.out[meta[2 * lane + 1]] = (code <= 0 || bad[lane] != 0) ? __builtin_nan("") : acc[lane];
+            double tot = acc[lane];
+            if constexpr (COOP)
+                for (int w = 1; w < wpb; ++w) tot += acc[w * sb + lane];
+            a.out[meta[2 * lane + 1]] = (code <= 0 || bad[lane] != 0) ? __builtin_nan("") : tot;
         }
     }
     // The last wave to leave resets the counters for the next launch, so no
@@ -709,6 +763,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GMAX =
     // the block out (one global atomic per block, not per wave: 0.627 -> 0.611
     // ms at c3), so when the count reaches the number of blocks no wave of this
     // launch touches the queue again.
+    if (COOP && (int64_t)gridDim.x >= a.n_items) return;     // the queue was not used
     if (lane == 0 && atomicAdd(&waves_out, 1u) == (blockDim.x >> 6) - 1) {
         if (atomicAdd(a.queue + kQueueDone, 1u) == gridDim.x - 1) {
             for (int q = 0; q < kRaggedQueues; ++q) atomicExch(a.queue + q * kQueueStride, 0u);
@@ -719,81 +774,167 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GMAX =
 
 // ------------------------------------------------------- ragged, no allocation
 // Device memory of the allocation-free ragged entry point: the work-queue
-// and exit counters in the first 256 bytes, then the int32 work order of up to
-// kStaticMaxSys systems.  One copy per GPU, kept until the process ends; every
-// call on a GPU shares it (calls that overlap in time on one GPU race).
+// and exit counters in the first 2 KiB, the blocks' counts of systems per planet
+// count, then the int32 work order of up to kStaticMaxSys systems.  One copy per
+// GPU, kept until the process ends; every call on a GPU shares it (calls that
+// overlap in time on one GPU race).
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
-constexpr int kPrepThreads = 1024;
+// The work order: systems by decreasing planet count (so that the systems of a
+// work item share their planet count), index order within a count (a stable
+// counting sort: the order, and so every result, is the same on every call), the
+// systems whose CSR offsets fail the check (0 <= o0 <= o1 <= n_obs_total,
+// 0 <= p0 < p1 <= n_pl_total, p1 - p0 <= kMaxPl) last as -1 - index.
+//
+// Two launches of one block per kPrepTile systems: the first checks the offsets
+// and counts the tile's systems per key (and zeroes the queue counters), the
+// second sums the counts before its tile and places its systems.  Within a tile
+// the lanes read consecutive systems; ballots rank them.  One block that walked
+// all systems twice, each thread over a run of its own, took 93 us at 30,011
+// systems (strided 8-byte reads, one load in flight per thread): more than half
+// of the whole call.
+// Up to kStaticOneTile systems a single block of 1,024 threads does both (one
+// launch of 5 us instead of two).
+constexpr int kPrepThreads = 256;
 constexpr int kPrepKeys = kMaxPl + 1;      // planet counts 8 .. 1, then rejected systems
+constexpr int kPrepRounds = kStaticTile / kPrepThreads;
+constexpr int kOneThreads = 1024, kOneRounds = 8;
+constexpr int64_t kStaticOneTile = kOneThreads * kOneRounds;
+static_assert(kStaticCountBytes == (size_t)kPrepKeys * kStaticMaxTiles * sizeof(int), "counts fill their area");
 
-// One block: zeroes the queue counters, checks every system's CSR offsets
-// (0 <= o0 <= o1 <= n_obs_total, 0 <= p0 < p1 <= n_pl_total, p1 - p0 <= kMaxPl)
-// and writes the work order: systems by decreasing planet count (so that the
-// systems of a work item share their planet count), index order within a
-// count (a stable counting sort: the order, and so every result, is the same
-// on every call), the rejected systems last as -1 - index.  Thread t owns the
-// contiguous run of systems [t c, (t + 1) c).
-__global__ void __launch_bounds__(kPrepThreads) k_ragged_static_order(const int64_t *__restrict__ obs_off,
-                                                                      const int64_t *__restrict__ pl_off,
-                                                                      int64_t n_sys, int64_t n_obs_total,
-                                                                      int64_t n_pl_total, int32_t *__restrict__ order,
-                                                                      unsigned int *__restrict__ queue)
+struct StaticOrderArgs {
+    const int64_t *obs_off, *pl_off;
+    int64_t n_sys, n_obs_total, n_pl_total;
+    int n_tiles;
+    int *counts;               // [kPrepKeys][n_tiles]
+    int32_t *order;
+    unsigned int *queue;
+};
+
+// Key of system i: 0 for 8 planets ... 7 for one, 8 rejected.
+__device__ __forceinline__ int static_key(const StaticOrderArgs &a, int64_t i)
 {
-    __shared__ int wtot[kPrepKeys][kPrepThreads / 64];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    for (int q = t; q < kQueueWords; q += kPrepThreads) queue[q] = 0u;
-    const int64_t c = (n_sys + kPrepThreads - 1) / kPrepThreads;
-    const int64_t i0 = min(n_sys, (int64_t)t * c), i1 = min(n_sys, i0 + c);
-    auto key_of = [&](int64_t i) {
-        const int64_t o0 = obs_off[i], o1 = obs_off[i + 1], p0 = pl_off[i], p1 = pl_off[i + 1];
-        const bool ok = o0 >= 0 && o0 <= o1 && o1 <= n_obs_total && p0 >= 0 && p0 < p1 && p1 <= n_pl_total &&
-                        p1 - p0 <= kMaxPl;
-        return ok ? kMaxPl - (int)(p1 - p0) : kMaxPl;      // 0 for 8 planets ... 7 for one, 8 rejected
-    };
-    int cnt[kPrepKeys];
+    const int64_t o0 = a.obs_off[i], o1 = a.obs_off[i + 1], p0 = a.pl_off[i], p1 = a.pl_off[i + 1];
+    const bool ok = o0 >= 0 && o0 <= o1 && o1 <= a.n_obs_total && p0 >= 0 && p0 < p1 && p1 <= a.n_pl_total &&
+                    p1 - p0 <= kMaxPl;
+    return ok ? kMaxPl - (int)(p1 - p0) : kMaxPl;
+}
+
+// The keys of this thread's ROUNDS systems (-1 past the last), and in LDS how
+// many of each key every (round, wavefront) segment of the block's tile of
+// THREADS x ROUNDS systems holds.
+template <int THREADS, int ROUNDS>
+__device__ __forceinline__ void static_tile_keys(const StaticOrderArgs &a, int (&key)[ROUNDS], int (*seg)[kPrepKeys])
+{
+    const int lane = __lane_id(), w = threadIdx.x >> 6;
+    const int64_t base = (int64_t)blockIdx.x * (THREADS * ROUNDS);
 #pragma unroll
-    for (int k = 0; k < kPrepKeys; ++k) cnt[k] = 0;
-    for (int64_t i = i0; i < i1; ++i) {
-        const int k = key_of(i);
-#pragma unroll
-        for (int q = 0; q < kPrepKeys; ++q) cnt[q] += (q == k);
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int64_t i = base + r * THREADS + threadIdx.x;
+        key[r] = i < a.n_sys ? static_key(a, i) : -1;
     }
-    // exclusive prefix of every key's count over the threads (wave scans, then the waves)
-    int pre[kPrepKeys];
 #pragma unroll
-    for (int k = 0; k < kPrepKeys; ++k) {
-        int incl = cnt[k];
-        for (int d = 1; d < 64; d <<= 1) {
-            const int u = __shfl_up(incl, d, 64);
-            if (lane >= d) incl += u;
+    for (int r = 0; r < ROUNDS; ++r) {
+        int n = 0;
+#pragma unroll
+        for (int k = 0; k < kPrepKeys; ++k) {
+            const int c = __popcll(__ballot(key[r] == k));
+            n = lane == k ? c : n;
         }
-        pre[k] = incl - cnt[k];
-        if (lane == 63) wtot[k][w] = incl;
+        if (lane < kPrepKeys) seg[r * (THREADS / 64) + w][lane] = n;
     }
     __syncthreads();
-    int64_t base = 0;
-#pragma unroll
-    for (int k = 0; k < kPrepKeys; ++k) {
-        int64_t tot = 0, before = 0;
-        for (int q = 0; q < kPrepThreads / 64; ++q) {
-            tot += wtot[k][q];
-            if (q < w) before += wtot[k][q];
-        }
-        cnt[k] = (int)(base + before + pre[k]);          // this thread's first slot for key k
-        base += tot;
+}
+
+__global__ void __launch_bounds__(kPrepThreads) k_ragged_static_count(StaticOrderArgs a)
+{
+    constexpr int kSegs = kStaticTile / 64;
+    __shared__ int seg[kSegs][kPrepKeys];
+    int key[kPrepRounds];
+    if (blockIdx.x == 0)
+        for (int q = threadIdx.x; q < kQueueWords; q += kPrepThreads) a.queue[q] = 0u;
+    static_tile_keys<kPrepThreads, kPrepRounds>(a, key, seg);
+    if (threadIdx.x < kPrepKeys) {
+        int n = 0;
+        for (int q = 0; q < kSegs; ++q) n += seg[q][threadIdx.x];
+        a.counts[threadIdx.x * a.n_tiles + blockIdx.x] = n;
     }
-    for (int64_t i = i0; i < i1; ++i) {
-        const int k = key_of(i);
-        int slot = 0;
+}
+
+// ONE: a single tile, whose own counts are all there are (no counting launch).
+template <int THREADS, int ROUNDS, bool ONE>
+__global__ void __launch_bounds__(THREADS) k_ragged_static_place(StaticOrderArgs a)
+{
+    constexpr int kWaves = THREADS / 64, kSegs = ROUNDS * kWaves;
+    __shared__ int seg[kSegs][kPrepKeys];
+    __shared__ int tot[kPrepKeys], before[kPrepKeys];
+    const int lane = __lane_id(), w = threadIdx.x >> 6, tile = blockIdx.x;
+    int key[ROUNDS];
+    if constexpr (ONE) {
+        for (int q = threadIdx.x; q < kQueueWords; q += THREADS) a.queue[q] = 0u;
+    } else {
+        // each key's count over all tiles and over the tiles before this one
+        for (int k = w; k < kPrepKeys; k += kWaves) {
+            int t = 0, b = 0;
+            for (int q = lane; q < a.n_tiles; q += 64) {
+                const int c = a.counts[k * a.n_tiles + q];
+                t += c;
+                b += q < tile ? c : 0;
+            }
 #pragma unroll
-        for (int q = 0; q < kPrepKeys; ++q) {
-            if (q == k) {
-                slot = cnt[q];
-                cnt[q] += 1;
+            for (int o = 32; o >= 1; o >>= 1) {
+                t += __shfl_xor(t, o, 64);
+                b += __shfl_xor(b, o, 64);
+            }
+            if (lane == 0) {
+                tot[k] = t;
+                before[k] = b;
             }
         }
-        order[slot] = k < kMaxPl ? (int32_t)i : (int32_t)(-1 - i);
+    }
+    static_tile_keys<THREADS, ROUNDS>(a, key, seg);
+    // every (segment, key)'s first slot within the key, in place of its count: one
+    // wavefront per key, lanes over the segments
+    for (int k = w; k < kPrepKeys; k += kWaves) {
+        int carry = 0;
+        for (int q0 = 0; q0 < kSegs; q0 += 64) {
+            const int n = q0 + lane < kSegs ? seg[q0 + lane][k] : 0;
+            int incl = n;
+            for (int d = 1; d < 64; d <<= 1) {
+                const int u = __shfl_up(incl, d, 64);
+                if (lane >= d) incl += u;
+            }
+            if (q0 + lane < kSegs) seg[q0 + lane][k] = carry + incl - n;
+            carry += __shfl(incl, 63, 64);
+        }
+        if (ONE && lane == 0) {
+            tot[k] = carry;
+            before[k] = 0;
+        }
+    }
+    __syncthreads();
+    const uint64_t below_me = (1ull << lane) - 1ull;
+    int base[kPrepKeys];                       // first slot of this tile's systems of each key
+#pragma unroll
+    for (int k = 0, sum = 0; k < kPrepKeys; ++k) {
+        base[k] = sum + before[k];
+        sum += tot[k];
+    }
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int64_t i = (int64_t)tile * (THREADS * ROUNDS) + r * THREADS + threadIdx.x;
+        uint64_t same = 0;
+        int slot = 0;
+#pragma unroll
+        for (int k = 0; k < kPrepKeys; ++k) {
+            const uint64_t m = __ballot(key[r] == k);
+            same = key[r] == k ? m : same;
+            slot = key[r] == k ? base[k] : slot;
+        }
+        if (key[r] >= 0) {
+            slot += seg[r * kWaves + w][key[r]] + __popcll(same & below_me);
+            a.order[slot] = key[r] < kMaxPl ? (int32_t)i : (int32_t)(-1 - i);
+        }
     }
 }
 
@@ -820,6 +961,25 @@ hipError_t static_scratch(void **ptr)
     return hipSuccess;
 }
 
+static size_t ragged_coop_lds(int block, int sb);
+
+// One block per item (k_ragged_mixed's COOP form, two-chunk units: five blocks a
+// CU where four-chunk units leave four; 30,011 systems 69 -> 64 us).  Eight
+// wavefronts a block while two blocks a CU hold every item, else four (32 items:
+// 25 against 35 us, 501: 29 against 38, 1,876: 84 against 64).
+static hipError_t launch_ragged_coop(RaggedArgs a, LaunchShape shape, hipStream_t st)
+{
+    a.gmax = 2;
+    const int block = shape.block > 0 ? shape.block : a.n_items <= 2 * (int64_t)device_cu_count() ? 512 : 256;
+    const size_t lds = ragged_coop_lds(block, a.sb);
+    int per_cu = shape.blocks_per_cu;
+    if (per_cu <= 0) per_cu = cached_occupancy((const void *)k_ragged_mixed<2, true>, block, lds);
+    const int64_t cap = (int64_t)device_cu_count() * per_cu;
+    const int grid = (int)(a.n_items < cap ? a.n_items : cap);
+    hipLaunchKernelGGL((k_ragged_mixed<2, true>), dim3(grid), dim3(block), lds, st, a);
+    return hipGetLastError();
+}
+
 hipError_t launch_ragged_static(RaggedArgs a, LaunchShape shape, hipStream_t st)
 {
     if (a.n_sys <= 0) return hipSuccess;
@@ -827,19 +987,40 @@ hipError_t launch_ragged_static(RaggedArgs a, LaunchShape shape, hipStream_t st)
     void *base = nullptr;
     hipError_t err = static_scratch(&base);
     if (err != hipSuccess) return err;
-    unsigned int *queue = reinterpret_cast<unsigned int *>(base);
-    int32_t *order = reinterpret_cast<int32_t *>(reinterpret_cast<unsigned char *>(base) + kStaticQueueBytes);
-    hipLaunchKernelGGL(k_ragged_static_order, dim3(1), dim3(kPrepThreads), 0, st, a.obs_off, a.pl_off, a.n_sys,
-                       a.n_obs_total, a.n_pl_total, order, queue);
+    unsigned char *area = reinterpret_cast<unsigned char *>(base);
+    unsigned int *queue = reinterpret_cast<unsigned int *>(area);
+    int32_t *order = reinterpret_cast<int32_t *>(area + kStaticQueueBytes + kStaticCountBytes);
+    StaticOrderArgs o;
+    o.obs_off = a.obs_off;
+    o.pl_off = a.pl_off;
+    o.n_sys = a.n_sys;
+    o.n_obs_total = a.n_obs_total;
+    o.n_pl_total = a.n_pl_total;
+    o.n_tiles = (int)((a.n_sys + kStaticTile - 1) / kStaticTile);
+    o.counts = reinterpret_cast<int *>(area + kStaticQueueBytes);
+    o.order = order;
+    o.queue = queue;
+    if (a.n_sys <= kStaticOneTile) {
+        hipLaunchKernelGGL((k_ragged_static_place<kOneThreads, kOneRounds, true>), dim3(1), dim3(kOneThreads), 0, st, o);
+    } else {
+        hipLaunchKernelGGL(k_ragged_static_count, dim3(o.n_tiles), dim3(kPrepThreads), 0, st, o);
+        err = hipGetLastError();
+        if (err != hipSuccess) return err;
+        hipLaunchKernelGGL((k_ragged_static_place<kPrepThreads, kPrepRounds, false>), dim3(o.n_tiles),
+                           dim3(kPrepThreads), 0, st, o);
+    }
     err = hipGetLastError();
     if (err != hipSuccess) return err;
     a.order = order;
     a.queue = queue;
     a.n_items = (a.n_sys + a.sb - 1) / a.sb;
-    const int block = shape.block > 0 ? shape.block : 256;
-    const int wpb = block / 64;
-    const int64_t need = (a.n_items + wpb - 1) / wpb;
+    const int wpb = (shape.block > 0 ? shape.block : 256) / 64;
     const int64_t cap = ragged_max_grid(shape, a.sb, a.gmax);
+    // a block per item up to two items for every three resident wavefronts (256
+    // threads, items of 16: 30,011 systems 84 against 111 us a call, 65,536 systems
+    // 144 against 134, 262,144 systems 721 against 644)
+    if (wpb > 1 && 3 * a.n_items < 2 * cap * wpb) return launch_ragged_coop(a, shape, st);
+    const int64_t need = (a.n_items + wpb - 1) / wpb;
     const int grid = (int)(need < cap ? need : cap);
     return launch_ragged(a, shape, grid, st);
 }
@@ -1007,6 +1188,11 @@ static size_t ragged_lds(int block, int sb)
     return (size_t)(block / 64) * ragged_lds_per_wave(sb);
 }
 
+static size_t ragged_coop_lds(int block, int sb)
+{
+    return ragged_lds_per_wave(sb) + (size_t)(block / 64) * sb * sizeof(double);
+}
+
 // The block's LDS is the waves' dynamic slices plus the static copy of the
 // Kepler starting-value table and the block's two queue words (16 bytes
 // allowed for them and their alignment).
@@ -1017,7 +1203,7 @@ int ragged_max_grid(LaunchShape shape, int sb, int gmax)
     const int block = shape.block > 0 ? shape.block : 256;
     int per_cu = shape.blocks_per_cu;
     if (per_cu <= 0) {
-        void (*kern)(RaggedArgs) = gmax == 2 ? k_ragged_mixed<2> : k_ragged_mixed<4>;
+        void (*kern)(RaggedArgs) = gmax == 2 ? k_ragged_mixed<2, false> : k_ragged_mixed<4, false>;
         per_cu = cached_occupancy((const void *)kern, block, ragged_lds(block, sb));
     }
     return device_cu_count() * per_cu;
@@ -1027,9 +1213,9 @@ hipError_t launch_ragged(RaggedArgs a, LaunchShape shape, int grid, hipStream_t 
 {
     const int block = shape.block > 0 ? shape.block : 256;
     if (a.gmax == 2)
-        hipLaunchKernelGGL(k_ragged_mixed<2>, dim3(grid > 0 ? grid : 1), dim3(block), ragged_lds(block, a.sb), st, a);
+        hipLaunchKernelGGL((k_ragged_mixed<2, false>), dim3(grid > 0 ? grid : 1), dim3(block), ragged_lds(block, a.sb), st, a);
     else
-        hipLaunchKernelGGL(k_ragged_mixed<4>, dim3(grid > 0 ? grid : 1), dim3(block), ragged_lds(block, a.sb), st, a);
+        hipLaunchKernelGGL((k_ragged_mixed<4, false>), dim3(grid > 0 ? grid : 1), dim3(block), ragged_lds(block, a.sb), st, a);
     return hipGetLastError();
 }
 
