@@ -53,6 +53,14 @@ constexpr size_t dense_table_bytes()
     return (Pol::kTables >= 1 ? sizeof(kep_start_tab) : 0) + (Pol::kTables == 2 ? kSc64Bytes : 0);
 }
 
+// k_dense_team: the block's records, every wavefront's sums and the domain flags,
+// then the tables.
+__host__ __device__ inline size_t team_table_offset(int W, int sb, int n_pl, size_t rec_size)
+{
+    return ((size_t)sb * n_pl * rec_size + (size_t)W * sb * sizeof(double) + (size_t)sb * sizeof(int) + 15) &
+           ~(size_t)15;
+}
+
 template <class Pol, int NCH, int MODE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dense_waves_per_simd<Pol, NCH>())))
 k_dense(DenseArgs a)
@@ -209,6 +217,107 @@ k_dense(DenseArgs a)
                 bool bad = sbad || __any(bad_obs);
                 if (lane == 0) a.out[sys] = bad ? __builtin_nan("") : tot;
             }
+        }
+    }
+}
+
+// Chi-square with several wavefronts over a system's observations: wavefront w of
+// a team of W holds groups w, w + W, ... of NCH x 64 observations, the team's
+// wavefronts evaluate the same systems, and the block adds their sums in wavefront
+// order.  A block of T teams shares the tables and a batch of systems (records
+// built by all its threads, systems dealt to the teams in turn).  For two kinds of
+// call:
+//   - more than 256 observations: one wavefront per system held eight chunks
+//     (212 VGPRs, two wavefronts per SIMD, and a whole eight for the last few),
+//     or beyond 512 loaded and converted every observation again for every
+//     system; here each wavefront keeps its group in registers for the launch (up to
+//     16 x 4 x 64 observations), or loads it once per batch;
+//   - few systems: a system's observations one wavefront after another leave most
+//     SIMDs idle.
+// Every observation is evaluated as by k_dense, so results differ from its only
+// in the order of the binary64 sums.
+template <class Pol, int NCH>
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(dense_waves_per_simd<Pol, NCH>())))
+k_dense_team(DenseArgs a, int W)
+{
+    using Rec = typename Pol::Rec;
+    using Obs = typename Pol::Obs;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = __lane_id();
+    const int T = uniform_int((int)(blockDim.x >> 6) / W);
+    const int team = uniform_int((int)(threadIdx.x >> 6) / W);
+    const int w = uniform_int((int)(threadIdx.x >> 6)) - team * W;
+    Rec *recs = reinterpret_cast<Rec *>(smem);
+    double *part = reinterpret_cast<double *>(recs + (size_t)a.sb * a.n_pl);    // [W][sb]
+    int *sysbad = reinterpret_cast<int *>(part + (size_t)W * a.sb);
+    uint32_t *tab = reinterpret_cast<uint32_t *>(smem + team_table_offset(W, a.sb, a.n_pl, sizeof(Rec)));
+    double2 *knots = nullptr;
+    const int64_t n_batches = (a.n_sys + a.sb - 1) / a.sb;
+    const int n_groups = (int)((a.n_obs + 64 * NCH - 1) / (64 * NCH));
+    const bool has_jit = a.jitter != nullptr;
+
+    Obs o[NCH];
+    auto load_group = [&](int g) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) Pol::load_obs(a, (int64_t)g * 64 * NCH + c * 64 + lane, o[c]);
+    };
+    if (n_groups <= W) load_group(w);
+    if constexpr (Pol::kTables == 2) {
+        knots = reinterpret_cast<double2 *>(tab + kTabWords);
+        load_knots64(knots);
+    }
+    load_start_table(tab);       // ends with the block barrier
+
+    for (int64_t bt = blockIdx.x; bt < n_batches; bt += gridDim.x) {
+        const int64_t s0 = bt * a.sb;
+        const int nb = (int)min((int64_t)a.sb, a.n_sys - s0);
+        __syncthreads();                                   // the previous batch's sums are written out
+        for (int q = threadIdx.x; q < nb; q += blockDim.x) {
+            const int64_t sys = s0 + q;
+            bool ok = isfinite(a.t0);
+            if (a.offset) ok = ok && isfinite(a.offset[sys]);
+            if (has_jit) ok = ok && isfinite(a.jitter[sys]) && a.jitter[sys] >= 0.0;
+            sysbad[q] = ok ? 0 : 1;
+        }
+        __syncthreads();
+        for (int q = threadIdx.x; q < nb * a.n_pl; q += blockDim.x) {
+            const int j = q / nb, sq = q - j * nb;
+            const int64_t p = (int64_t)j * a.n_sys + s0 + sq;
+            Rec r;
+            if (!Pol::setup(a, a.P[p], a.K[p], a.e[p], a.w[p], a.M0[p], r)) sysbad[sq] = 1;
+            recs[sq * a.n_pl + j] = r;
+        }
+        __syncthreads();
+
+        for (int g = w; g < n_groups; g += W) {
+            if (n_groups > W) load_group(g);
+            for (int s = team; s < nb; s += T) {
+                const double gam = a.offset ? a.offset[s0 + s] : 0.0;
+                const double jit = has_jit ? a.jitter[s0 + s] : 0.0;
+                typename Pol::ModelAcc m[NCH];
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) Pol::model_init(m[c]);
+                for (int j = 0; j < a.n_pl; ++j) pol_add_planet<Pol, NCH>(recs[s * a.n_pl + j], o, m, a, tab, knots);
+                typename Pol::ChiAcc chi;
+                Pol::chi_init(chi);
+                bool bad_obs = false;
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) {
+                    if (o[c].in) {
+                        const bool okw = Pol::chi_add(chi, m[c], o[c], gam, jit, has_jit);
+                        bad_obs = bad_obs || !okw || !o[c].ok;
+                    }
+                }
+                double tot = wave_sum(Pol::chi_value(chi));
+                if (__any(bad_obs)) tot = __builtin_nan("");
+                if (lane == 0) part[w * a.sb + s] = g == w ? tot : part[w * a.sb + s] + tot;
+            }
+        }
+        __syncthreads();
+        for (int q = threadIdx.x; q < nb; q += blockDim.x) {
+            double tot = part[q];
+            for (int v = 1; v < W; ++v) tot += part[v * a.sb + q];
+            a.out[s0 + q] = sysbad[q] != 0 ? __builtin_nan("") : tot;
         }
     }
 }
@@ -1082,6 +1191,72 @@ hipError_t launch_kepler_solve(const double *M, const double *e, double *E, int6
     return hipGetLastError();
 }
 
+// How many chunks a wavefront takes (NCH) and how many wavefronts share a
+// system's observations (W): the least of rounds x instructions x the time each
+// takes.  A wavefront's instructions per system are about 62 a planet and chunk,
+// 25 a planet, 10 a chunk and 45 more (the mixed kernel's; the proportions are
+// what matters); a SIMD issues for its wavefronts in turn, and a lone one at half
+// that rate.  Large batches get the NCH that fits n_obs with the fewest empty
+// chunks (157 observations: three, not four), small ones more wavefronts per
+// system.
+struct DenseSplit {
+    int nch, W;
+};
+
+static DenseSplit dense_split(int64_t n_sys, int n_pl, int64_t n_obs)
+{
+    const int64_t need = n_obs > 64 ? (n_obs + 63) / 64 : 1;
+    const double simds = 4.0 * device_cu_count();
+    DenseSplit best{1, 1};
+    double best_cost = 0.0;
+    for (int nch = 4; nch >= 1; --nch) {
+        const int64_t groups = (need + nch - 1) / nch;
+        const int W = (int)(groups < 16 ? groups : 16);
+        const double instr = n_pl * (62.0 * nch + 25.0) + 10.0 * nch + 45.0;
+        const double cost = (double)((groups + W - 1) / W) * instr * fmax(2.0, (double)n_sys * W / simds);
+        if (nch == 4 || cost < best_cost) {
+            best = DenseSplit{nch, W};
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+template <class Pol>
+static hipError_t launch_dense_team(DenseArgs a, DenseSplit split, LaunchShape shape, hipStream_t st)
+{
+    int W = shape.block > 0 ? shape.block / 64 : split.W;
+    const int64_t groups = (a.n_obs + 64 * split.nch - 1) / (64 * split.nch);
+    if (W > groups) W = (int)(groups > 0 ? groups : 1);
+    auto lds_of = [&](int64_t sb) {
+        return team_table_offset(W, (int)sb, a.n_pl, sizeof(typename Pol::Rec)) + dense_table_bytes<Pol>();
+    };
+    // teams per block: four wavefronts share the tables (two teams of two: one team
+    // left no room for records, 60,000 x 4 x 300 256 us against 152; two teams of
+    // three, six wavefronts on four SIMDs, 30,000 x 4 x 700 228 against 162), unless
+    // the systems do not fill the chip that way.  Systems per batch: the blocks that the
+    // registers allow (four or five wavefronts per SIMD) share a CU's LDS, at most
+    // sixteen systems a team (whole 128-byte lines of the parameter planes)
+    const int64_t cus = device_cu_count();
+    const int T = W <= 2 && a.n_sys >= 8 * cus ? 4 / W : 1;
+    const int blocks = 4 * dense_waves_per_simd<Pol, 4>() / (T * W);
+    int64_t sb_cap = 16 * T;
+    while (sb_cap > 1 && (int64_t)lds_of(sb_cap) > lds_budget(blocks > 1 ? blocks : 1)) --sb_cap;
+    void (*kern)(DenseArgs, int) = split.nch == 1   ? k_dense_team<Pol, 1>
+                                   : split.nch == 2 ? k_dense_team<Pol, 2>
+                                   : split.nch == 3 ? k_dense_team<Pol, 3>
+                                                    : k_dense_team<Pol, 4>;
+    int per_cu = shape.blocks_per_cu;
+    if (per_cu <= 0) per_cu = cached_occupancy((const void *)kern, 64 * T * W, lds_of(sb_cap));
+    const int64_t cap = cus * per_cu;
+    // a multiple of T systems keeps the teams level
+    a.sb = T * systems_per_batch((a.n_sys + T - 1) / T, cap, sb_cap / T > 0 ? sb_cap / T : 1);
+    const int64_t n_batches = (a.n_sys + a.sb - 1) / a.sb;
+    const int64_t grid = n_batches < cap ? n_batches : cap;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * T * W), lds_of(a.sb), st, a, W);
+    return hipGetLastError();
+}
+
 template <class Pol, int MODE>
 static hipError_t launch_dense_t(DenseArgs a, LaunchShape shape, hipStream_t st)
 {
@@ -1104,27 +1279,38 @@ static hipError_t launch_dense_t(DenseArgs a, LaunchShape shape, hipStream_t st)
     // a line split between two batches may be fetched by two XCDs' L2s
     if (sb_cap > 16) sb_cap &= ~(int64_t)15;
     size_t lds = lds_of(sb_cap);
-    const int nch_needed = (int)((a.n_obs + 63) / 64);
+    const int64_t need = a.n_obs > 64 ? (a.n_obs + 63) / 64 : 1;
     void (*kern)(DenseArgs);
     int nch;
-    if (nch_needed <= 1) { kern = k_dense<Pol, 1, MODE>; nch = 1; }
-    else if (nch_needed <= 2) { kern = k_dense<Pol, 2, MODE>; nch = 2; }
-    else if (nch_needed <= 4) { kern = k_dense<Pol, 4, MODE>; nch = 4; }
-    else if constexpr (Pol::kTables == 2) { kern = k_dense<Pol, 4, MODE>; nch = 4; }   // eight: 256 VGPRs, one wavefront
-    else { kern = k_dense<Pol, 8, MODE>; nch = 8; }
+    if constexpr (table) {
+        // one to four chunks a lane (velocities of more observations go out in equal
+        // groups of at most four, each a work item)
+        const int64_t groups = (need + 3) / 4;
+        nch = (int)((need + groups - 1) / groups);
+        if constexpr (MODE == kChi2) {
+            const DenseSplit split = dense_split(a.n_sys, a.n_pl, a.n_obs);
+            if (groups > 1 || (split.W > 1 && shape.block == 0)) return launch_dense_team<Pol>(a, split, shape, st);
+        }
+        kern = nch == 1   ? k_dense<Pol, 1, MODE>
+               : nch == 2 ? k_dense<Pol, 2, MODE>
+               : nch == 3 ? k_dense<Pol, 3, MODE>
+                          : k_dense<Pol, 4, MODE>;
+    } else {
+        nch = need <= 1 ? 1 : need <= 2 ? 2 : need <= 4 ? 4 : 8;
+        kern = nch == 1   ? k_dense<Pol, 1, MODE>
+               : nch == 2 ? k_dense<Pol, 2, MODE>
+               : nch == 4 ? k_dense<Pol, 4, MODE>
+                          : k_dense<Pol, 8, MODE>;
+    }
     int per_cu = shape.blocks_per_cu;
     if (per_cu <= 0) {
         per_cu = cached_occupancy((const void *)kern, block, lds);
     }
-    const int64_t max_waves = (int64_t)device_cu_count() * per_cu * wpb;
-    // ceil: every wave gets at most one batch when the cap allows it, so no wave
-    // runs a second batch while the others idle
-    const int64_t mw = max_waves > 0 ? max_waves : 1;
-    int64_t sb = (a.n_sys + mw - 1) / mw;
-    sb = sb < 1 ? 1 : (sb > sb_cap ? sb_cap : sb);
-    a.sb = (int)sb;
-    lds = lds_of(sb);
-    const int64_t n_batches = (a.n_sys + sb - 1) / sb;
+    // every round as full as the others: 100,003 systems in batches of the full 16
+    // were 6,251 batches on 5,120 wavefronts, two rounds with the second a fifth full
+    a.sb = systems_per_batch(a.n_sys, (int64_t)device_cu_count() * per_cu * wpb, sb_cap);
+    lds = lds_of(a.sb);
+    const int64_t n_batches = (a.n_sys + a.sb - 1) / a.sb;
     const int64_t n_groups = (a.n_obs + 64 * nch - 1) / (64 * nch);
     const int64_t n_items = MODE != kChi2 ? n_batches * (n_groups > 0 ? n_groups : 1) : n_batches;
     int64_t grid = (n_items + wpb - 1) / wpb;
