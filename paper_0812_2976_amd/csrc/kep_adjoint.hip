@@ -22,6 +22,8 @@
 // the rows are written.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "kep_device.h"
 #include "kep_grad.h"
 #include "kep_internal.h"
@@ -44,7 +46,10 @@ __host__ __device__ inline size_t adj_knots_offset(int wpb, int sb, int npl)
     return adj_table_offset(wpb, sb, npl) + ((sizeof(kep_start_tab) + 15) & ~(size_t)15);
 }
 
-template <int NPL, int NCH>
+// NCH chunks of 64 observations a group; LAST: the chunks of the last group of
+// several (its empty chunks only add zeros: leaving them out changes no bit), 0
+// where one group holds every observation.
+template <int NPL, int NCH, int LAST>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k_grad_obs(DenseArgs a, int nll)
 {
     constexpr int NROW = 5 * NPL + 1;
@@ -61,8 +66,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
     fill_sincos64_knots(knots);
     load_start_table(tab);          // ends with the block barrier
 
-    const SysShare share = sys_share<false>(a.n_sys, wpb, wib, a.sb);
-    const int n_groups = (int)((a.n_obs + 64 * NCH - 1) / (64 * NCH));
+    // groups of NCH chunks, before the last one where that has fewer
+    const int n_full = LAST > 0 ? (int)((a.n_obs + 64 * NCH - 1) / (64 * NCH)) - (LAST < NCH ? 1 : 0)
+                                : (a.n_obs > 0 ? 1 : 0);
     const bool has_jit = a.jitter != nullptr;
     const int row = lane / SPAN;
     const double nan = __builtin_nan("");
@@ -72,14 +78,17 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
 #pragma unroll
         for (int c = 0; c < NCH; ++c) load_obs_g(a, (int64_t)g * 64 * NCH + c * 64 + lane, o[c]);
     };
-    if (n_groups <= 1) load_group(0);
+    if (LAST == 0) load_group(0);
 
-    for (int64_t run0 = share.lo; run0 < share.hi; run0 += share.step) {
-        int64_t first;
-        const int nb = share_run(share, run0, a.sb, first);
+    // batches in turn over the grid's wavefronts: the whole grid sweeps the systems in
+    // order (contiguous shares per wavefront or block ran 2-7% slower: the grid then
+    // writes all over every output row at once)
+    for (int64_t bt = (int64_t)blockIdx.x * wpb + wib; bt < a.bt.n_batches; bt += (int64_t)gridDim.x * wpb) {
+        int nb;
+        const int64_t first = a.bt.first(bt, a.n_sys, nb);
         wave_sync_lds();
         if (lane < nb) {
-            const int64_t sys = first + (int64_t)share.stride * lane;
+            const int64_t sys = first + lane;
             bool ok = isfinite(a.t0);
             if (a.offset) ok = ok && isfinite(a.offset[sys]);
             if (has_jit) ok = ok && isfinite(a.jitter[sys]) && a.jitter[sys] >= 0.0;
@@ -92,7 +101,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
 #pragma nounroll
         for (int q = lane; q < nb * NPL; q += 64) {
             const int j = q / nb, sq = q - j * nb;
-            const int64_t p = (int64_t)j * a.n_sys + first + (int64_t)share.stride * sq;
+            const int64_t p = (int64_t)j * a.n_sys + first + sq;
             RecGrad r;
             if (!grad_setup_rec(a.fixed_iter, a.P[p], a.K[p], a.e[p], a.w[p], a.M0[p], r)) sysbad[sq] = 1;
             recs[sq * NPL + j] = r;
@@ -100,7 +109,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
         wave_sync_lds();
 
         for (int s = 0; s < nb; ++s) {
-            const int64_t sys = first + (int64_t)share.stride * s;
+            const int64_t sys = first + s;
             const double gam = a.offset ? a.offset[sys] : 0.0;
             const double jit = has_jit ? a.jitter[sys] : 0.0;
             const float jit2 = (float)(jit * jit);
@@ -109,36 +118,36 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
             double tot = 0.0;                        // this lane's row, summed over the groups
             double chi = 0.0, sum_lv = 0.0, sum_w = 0.0, sum_wr2 = 0.0;
             bool bad_obs = false;
-            for (int g = 0; g < n_groups; ++g) {
-                if (n_groups > 1) load_group(g);
+            auto group = [&](auto chunks) {
+                constexpr int NC = decltype(chunks)::value;
                 // pass 1: corrected velocities; sin E and cos E - e kept for pass 2.
                 // The planet loop is not unrolled (one copy of the Kepler solve in
                 // the code); its results go to registers by planet index.
-                double model[NCH];
-                float sE[NPL][NCH], cme[NPL][NCH];
+                double model[NC];
+                float sE[NPL][NC], cme[NPL][NC];
 #pragma unroll
-                for (int c = 0; c < NCH; ++c) model[c] = gam;
+                for (int c = 0; c < NC; ++c) model[c] = gam;
 #pragma nounroll
                 for (int j = 0; j < NPL; ++j) {
                     const RecGrad &rr = rs[j];
                     const Phase64 ph = rr.ph;
                     const Ecc32 k = rr.k;
-                    double M64[NCH];
-                    float M[NCH], E[NCH], sv[NCH], omc[NCH], sj[NCH], cj[NCH];
+                    double M64[NC];
+                    float M[NC], E[NC], sv[NC], omc[NC], sj[NC], cj[NC];
 #pragma unroll
-                    for (int c = 0; c < NCH; ++c) {
+                    for (int c = 0; c < NC; ++c) {
                         M64[c] = mean_anomaly64_exact(o[c].tt, ph);
                         M[c] = (float)M64[c];
                     }
-                    PolMixed::solve<NCH, false>(k, uniform_int(rr.niter), uniform_int(rr.check) != 0, rr.tp, M, E,
+                    PolMixed::solve<NC, false>(k, uniform_int(rr.niter), uniform_int(rr.check) != 0, rr.tp, M, E,
                                                 sv, omc, a.max_iter, tab);
 #pragma unroll
-                    for (int c = 0; c < NCH; ++c) model[c] += refine_velocity(rr, E[c], M64[c], knots, sj[c], cj[c]);
+                    for (int c = 0; c < NC; ++c) model[c] += refine_velocity(rr, E[c], M64[c], knots, sj[c], cj[c]);
 #pragma unroll
                     for (int jj = 0; jj < NPL; ++jj) {
                         if (jj == j) {
 #pragma unroll
-                            for (int c = 0; c < NCH; ++c) {
+                            for (int c = 0; c < NC; ++c) {
                                 sE[jj][c] = sj[c];
                                 cme[jj][c] = cj[c];
                             }
@@ -146,9 +155,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
                     }
                 }
                 // residuals and weights
-                float cw2[NCH];
+                float cw2[NC];
 #pragma unroll
-                for (int c = 0; c < NCH; ++c) {
+                for (int c = 0; c < NC; ++c) {
                     const double r = model[c] - o[c].v;
                     const float var = o[c].s2 + jit2;
                     const float w = rcp32(var);
@@ -175,7 +184,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
                     lds_reload_barrier();
                     const RecGrad &rr = rs[j];
 #pragma unroll
-                    for (int c = 0; c < NCH; ++c) {
+                    for (int c = 0; c < NC; ++c) {
                         float x[5];
                         grad_terms_ce(rr, sE[j][c], cme[j][c], (float)(o[c].tt * rr.ph.rP), x);
 #pragma unroll
@@ -183,8 +192,16 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
                     }
                 }
 #pragma unroll
-                for (int c = 0; c < NCH; ++c) acc[5 * NPL] += cw2[c];
+                for (int c = 0; c < NC; ++c) acc[5 * NPL] += cw2[c];
                 tot += (double)rows_reduce_scatter<R>(acc);
+            };
+            for (int g = 0; g < n_full; ++g) {
+                if (LAST > 0) load_group(g);
+                group(std::integral_constant<int, NCH>{});
+            }
+            if constexpr (LAST > 0 && LAST < NCH) {
+                load_group(n_full);
+                group(std::integral_constant<int, LAST>{});
             }
             chi = wave_sum(chi);
             if (nll) {
@@ -210,7 +227,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
     }
 }
 
-template <int NPL, int NCH>
+template <int NPL, int NCH, int LAST>
 hipError_t launch_grad_obs_t(DenseArgs a, bool nll, LaunchShape shape, hipStream_t st)
 {
     const int block = shape.block > 0 ? shape.block : 256;
@@ -224,31 +241,40 @@ hipError_t launch_grad_obs_t(DenseArgs a, bool nll, LaunchShape shape, hipStream
     sb_cap = sb_cap < 1 ? 1 : (sb_cap > kMaxSB ? kMaxSB : sb_cap);
     if (sb_cap > 8) sb_cap &= ~(int64_t)7;
     auto lds_of = [&](int64_t sb) { return adj_knots_offset(wpb, (int)sb, NPL) + kSc64Bytes; };
-    void (*kern)(DenseArgs, int) = k_grad_obs<NPL, NCH>;
+    void (*kern)(DenseArgs, int) = k_grad_obs<NPL, NCH, LAST>;
     int per_cu = shape.blocks_per_cu;
     if (per_cu <= 0) per_cu = cached_occupancy((const void *)kern, block, lds_of(sb_cap));
-    const int64_t max_waves = (int64_t)device_cu_count() * per_cu * wpb;
-    int64_t sb = (a.n_sys + max_waves - 1) / (max_waves > 0 ? max_waves : 1);
-    sb = sb < 1 ? 1 : (sb > sb_cap ? sb_cap : sb);
-    a.sb = (int)sb;
-    // one block per wpb x sb systems, at most the resident count
-    int64_t grid = (a.n_sys + (int64_t)wpb * sb - 1) / ((int64_t)wpb * sb);
+    a.bt = make_batches(a.n_sys, (int64_t)device_cu_count() * per_cu * wpb, sb_cap);
+    a.sb = a.bt.sb;
+    int64_t grid = (a.bt.n_batches + wpb - 1) / wpb;
     const int64_t cap = (int64_t)device_cu_count() * per_cu;
     if (grid > cap) grid = cap;
     if (grid < 1) grid = 1;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(block), lds_of(sb), st, a, nll ? 1 : 0);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(block), lds_of(a.sb), st, a, nll ? 1 : 0);
     return hipGetLastError();
 }
 
-// Observation chunks per lane: enough for n_obs in one group where the
+// Observation chunks per lane: as many as n_obs fills, in one group where the
 // registers allow (four chunks up to four planets, two beyond).
 template <int NPL>
 hipError_t launch_grad_obs_npl(DenseArgs a, bool nll, LaunchShape shape, hipStream_t st)
 {
     const int64_t need = (a.n_obs + 63) / 64;
-    if (need <= 1) return launch_grad_obs_t<NPL, 1>(a, nll, shape, st);
-    if (NPL > 4 || need <= 2) return launch_grad_obs_t<NPL, 2>(a, nll, shape, st);
-    return launch_grad_obs_t<NPL, (NPL <= 4 ? 4 : 2)>(a, nll, shape, st);
+    if (need <= 1) return launch_grad_obs_t<NPL, 1, 0>(a, nll, shape, st);
+    if (need == 2) return launch_grad_obs_t<NPL, 2, 0>(a, nll, shape, st);
+    if constexpr (NPL <= 4) {
+        if (need == 3) return launch_grad_obs_t<NPL, 3, 0>(a, nll, shape, st);
+        if (need == 4) return launch_grad_obs_t<NPL, 4, 0>(a, nll, shape, st);
+        switch (need % 4) {
+            case 1: return launch_grad_obs_t<NPL, 4, 1>(a, nll, shape, st);
+            case 2: return launch_grad_obs_t<NPL, 4, 2>(a, nll, shape, st);
+            case 3: return launch_grad_obs_t<NPL, 4, 3>(a, nll, shape, st);
+            default: return launch_grad_obs_t<NPL, 4, 4>(a, nll, shape, st);
+        }
+    } else {
+        return need % 2 ? launch_grad_obs_t<NPL, 2, 1>(a, nll, shape, st)
+                        : launch_grad_obs_t<NPL, 2, 2>(a, nll, shape, st);
+    }
 }
 
 }  // namespace

@@ -143,7 +143,6 @@ __global__ void __launch_bounds__(256) k_astro(AstroArgs a)
 
     const int64_t gw = (int64_t)blockIdx.x * wpb + wib;
     const int64_t n_waves = (int64_t)gridDim.x * wpb;
-    const int64_t n_batches = (a.n_sys + a.sb - 1) / a.sb;
     const int n_groups = (int)((a.n_obs + 64 * NCH - 1) / (64 * NCH));
     const int fixed = a.fixed_iter > 0 ? a.fixed_iter : (a.fixed_iter == 0 ? 30 : 0);
 
@@ -170,14 +169,14 @@ __global__ void __launch_bounds__(256) k_astro(AstroArgs a)
     };
     if (n_groups <= 1) load_group(0);
 
-    const int64_t n_items = MODEL ? n_batches * n_groups : n_batches;
+    const int64_t n_items = MODEL ? a.bt.n_batches * n_groups : a.bt.n_batches;
     int64_t prev_bt = -1;
     for (int64_t item = gw; item < n_items; item += n_waves) {
         const int64_t bt = MODEL ? item / n_groups : item;
         const int g_first = MODEL ? (int)(item - bt * n_groups) : 0;
         const int g_end = MODEL ? g_first + 1 : n_groups;
-        const int64_t s0 = bt * a.sb;
-        const int nb = (int)min((int64_t)a.sb, a.n_sys - s0);
+        int nb;
+        const int64_t s0 = a.bt.first(bt, a.n_sys, nb);
         if (bt != prev_bt) {
             prev_bt = bt;
             wave_sync_lds();
@@ -261,17 +260,15 @@ hipError_t launch_astro_t(AstroArgs a, LaunchShape shape, hipStream_t st)
     int nch;
     if (nch_needed <= 1) { kern = k_astro<KIND, 1, MODEL>; nch = 1; }
     else if (nch_needed <= 2) { kern = k_astro<KIND, 2, MODEL>; nch = 2; }
-    else { kern = k_astro<KIND, 4, MODEL>; nch = 4; }
+    else { kern = k_astro<KIND, 4, MODEL>; nch = 4; }   // (empty chunks are skipped: three ran no faster)
     int per_cu = shape.blocks_per_cu;
     if (per_cu <= 0) {
         per_cu = cached_occupancy((const void *)kern, block, rec_bytes * (size_t)sb_cap);
     }
-    const int64_t mw = (int64_t)device_cu_count() * per_cu * wpb;
-    int64_t sb = (a.n_sys + mw - 1) / (mw > 0 ? mw : 1);
-    sb = sb < 1 ? 1 : (sb > sb_cap ? sb_cap : sb);
-    a.sb = (int)sb;
-    const size_t lds = rec_bytes * (size_t)sb;
-    const int64_t n_batches = (a.n_sys + sb - 1) / sb;
+    a.bt = make_batches(a.n_sys, (int64_t)device_cu_count() * per_cu * wpb, sb_cap);
+    a.sb = a.bt.sb;
+    const size_t lds = rec_bytes * (size_t)a.sb;
+    const int64_t n_batches = a.bt.n_batches;
     const int64_t n_groups = (a.n_obs + 64 * nch - 1) / (64 * nch);
     const int64_t n_items = MODEL ? n_batches * (n_groups > 0 ? n_groups : 1) : n_batches;
     int64_t grid = (n_items + wpb - 1) / wpb;

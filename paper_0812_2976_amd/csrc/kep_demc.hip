@@ -139,7 +139,6 @@ __global__ void __launch_bounds__(256) k_demc_half(DenseArgs a, DemcArgs m, int 
 
     const int64_t gw = (int64_t)blockIdx.x * wpb + wib;
     const int64_t n_waves = (int64_t)gridDim.x * wpb;
-    const int64_t n_batches = (nh + sb - 1) / sb;
     const int n_groups = (int)((a.n_obs + 64 * NCH - 1) / (64 * NCH));
     const bool has_jit = a.jitter != nullptr;
 
@@ -150,9 +149,9 @@ __global__ void __launch_bounds__(256) k_demc_half(DenseArgs a, DemcArgs m, int 
     };
     if (n_groups <= 1) load_group(0);
 
-    for (int64_t bt = gw; bt < n_batches; bt += n_waves) {
-        const int64_t s0 = bt * sb;
-        const int nb = (int)min((int64_t)sb, nh - s0);
+    for (int64_t bt = gw; bt < a.bt.n_batches; bt += n_waves) {
+        int nb;
+        const int64_t s0 = a.bt.first(bt, nh, nb);
         wave_sync_lds();
         for (int c = lane; c < nb; c += 64) {                                   // A
             const U4 w = demc_draw(m.key0, m.key1, h, (uint32_t)(s0 + c), 0u, g);
@@ -273,15 +272,10 @@ static hipError_t launch_demc_half_t(DemcArgs m, DenseArgs a, int h, LaunchShape
         const size_t lds = (size_t)wpb * demc_lds_per_wave(sb_cap, a.n_pl, m.d, rec) + table;
         per_cu = cached_occupancy((const void *)kern, block, lds);
     }
-    const int64_t max_waves = (int64_t)device_cu_count() * per_cu * wpb;
-    // ceil: every wave gets at most one batch when the cap allows it, so no wave
-    // runs a second batch while the others idle
-    const int64_t mw = max_waves > 0 ? max_waves : 1;
-    int64_t sb = (m.nh + mw - 1) / mw;
-    sb = sb < 1 ? 1 : (sb > sb_cap ? sb_cap : sb);
-    a.sb = (int)sb;
+    a.bt = make_batches(m.nh, (int64_t)device_cu_count() * per_cu * wpb, sb_cap);
+    a.sb = a.bt.sb;
     const size_t lds = (size_t)wpb * demc_lds_per_wave(a.sb, a.n_pl, m.d, rec) + table;
-    const int64_t n_batches = (m.nh + sb - 1) / sb;
+    const int64_t n_batches = a.bt.n_batches;
     int64_t grid = (n_batches + wpb - 1) / wpb;
     const int64_t cap = (int64_t)device_cu_count() * per_cu;
     if (grid > cap) grid = cap;

@@ -257,7 +257,11 @@ __host__ __device__ inline size_t gn_obs_lds_per_wave(int sb)
     return (b + 15) & ~(size_t)15;
 }
 
-template <int NPL, int NCH>
+// GROUPS: kOneGroup where one group of NCH chunks holds every observation,
+// kOddChunks where the last group's last chunk is empty, else kGroups.
+enum { kOneGroup = 0, kGroups = 1, kOddChunks = 2 };
+
+template <int NPL, int NCH, int GROUPS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k_gn_obs(DenseArgs a, double *jtwr,
                                                                                        double *jtwj)
 {
@@ -280,8 +284,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
     fill_sincos64_knots(knots);
     __syncthreads();
 
-    const SysShare share = sys_share<true>(a.n_sys, wpb, wib, a.sb);
-    const int n_groups = (int)((a.n_obs + 64 * NCH - 1) / (64 * NCH));
+    // Block b takes runs b, b + G, ... of wpb x sb systems (G blocks); wavefront w of
+    // the block holds systems run + w + wpb i (i < nb), so the block's wavefronts
+    // write neighbouring systems' entries of every output row at about the same time
+    // and the L2 merges them into longer pieces (with consecutive systems per
+    // wavefront each row's line stays partly written for a whole batch and goes
+    // back to HBM in pieces; contiguous shares ran slower too).
+    const int64_t run_step = (int64_t)gridDim.x * wpb * a.sb;
+    const int n_groups = GROUPS == kOneGroup ? 1 : (int)((a.n_obs + 64 * NCH - 1) / (64 * NCH));
     const bool has_jit = a.jitter != nullptr;
     const double nan = __builtin_nan("");
     float *col = T + lane;                   // this lane's observation in column 0
@@ -305,12 +315,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
     };
     if (n_groups <= 1) load_group(0);
 
-    for (int64_t run0 = share.lo; run0 < share.hi; run0 += share.step) {
-        int64_t first;
-        const int nb = share_run(share, run0, a.sb, first);
+    for (int64_t run0 = (int64_t)blockIdx.x * wpb * a.sb; run0 < a.n_sys; run0 += run_step) {
+        const int64_t first = run0 + wib, left = a.n_sys - first;
+        const int nb = left <= 0 ? 0 : (int)min((int64_t)a.sb, (left + wpb - 1) / wpb);
         wave_sync_lds();
         if (lane < nb) {
-            const int64_t sys = first + (int64_t)share.stride * lane;
+            const int64_t sys = first + (int64_t)wpb * lane;
             bool ok = isfinite(a.t0);
             if (a.offset) ok = ok && isfinite(a.offset[sys]);
             if (has_jit) ok = ok && isfinite(a.jitter[sys]) && a.jitter[sys] >= 0.0;
@@ -321,7 +331,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
 #pragma nounroll
         for (int q = lane; q < nb * NPL; q += 64) {
             const int j = q / nb, sq = q - j * nb;
-            const int64_t p = (int64_t)j * a.n_sys + first + (int64_t)share.stride * sq;
+            const int64_t p = (int64_t)j * a.n_sys + first + (int64_t)wpb * sq;
             RecGrad r;
             if (!grad_setup_rec(a.fixed_iter, a.P[p], a.K[p], a.e[p], a.w[p], a.M0[p], r)) sysbad[sq] = 1;
             recs[sq * NPL + j] = r;
@@ -329,7 +339,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
         wave_sync_lds();
 
         for (int s = 0; s < nb; ++s) {
-            const int64_t sys = first + (int64_t)share.stride * s;
+            const int64_t sys = first + (int64_t)wpb * s;
             const double gam = a.offset ? a.offset[sys] : 0.0;
             const double jit = has_jit ? a.jitter[sys] : 0.0;
             const float jit2 = (float)(jit * jit);
@@ -376,6 +386,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
                 // the tile, then the tile's Gram matrix
 #pragma unroll
                 for (int c = 0; c < NCH; ++c) {
+                    // the last group's empty chunk has no rows
+                    if constexpr (GROUPS == kOddChunks)
+                        if (c == NCH - 1 && g == n_groups - 1) break;
                     const float var = o[c].s2 + jit2;
                     const bool use = o[c].in && o[c].ok && var > 0.0f;
                     if (o[c].in) bad_obs = bad_obs || !o[c].ok || !(var > 0.0f);
@@ -466,7 +479,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
     }
 }
 
-template <int NPL, int NCH>
+template <int NPL, int NCH, int GROUPS>
 hipError_t launch_gn_obs_t(DenseArgs a, double *jtwr, double *jtwj, LaunchShape shape, hipStream_t st)
 {
     const int block = shape.block > 0 ? shape.block : 256;
@@ -477,10 +490,11 @@ hipError_t launch_gn_obs_t(DenseArgs a, double *jtwr, double *jtwj, LaunchShape 
     int sb_cap = kMaxSB;
     while (sb_cap > 1 && (size_t)wpb * gn_obs_lds_per_wave<NPL>(sb_cap) > 40 * 1024) --sb_cap;
     auto lds_of = [&](int sbv) { return (size_t)wpb * gn_obs_lds_per_wave<NPL>(sbv) + kSc64Bytes; };
-    void (*kern)(DenseArgs, double *, double *) = k_gn_obs<NPL, NCH>;
+    void (*kern)(DenseArgs, double *, double *) = k_gn_obs<NPL, NCH, GROUPS>;
     int per_cu = shape.blocks_per_cu;
     if (per_cu <= 0) per_cu = cached_occupancy((const void *)kern, block, lds_of(sb_cap));
-    const int64_t max_waves = (int64_t)device_cu_count() * per_cu * wpb;
+    const int64_t cap = (int64_t)device_cu_count() * per_cu;
+    const int64_t max_waves = cap * wpb;
     int64_t sb = (a.n_sys + max_waves - 1) / (max_waves > 0 ? max_waves : 1);
     sb = sb < 1 ? 1 : (sb > sb_cap ? sb_cap : sb);
     a.sb = (int)sb;
@@ -488,7 +502,6 @@ hipError_t launch_gn_obs_t(DenseArgs a, double *jtwr, double *jtwj, LaunchShape 
     if (lds > 64 * 1024) return hipErrorInvalidValue;
     // one block per wpb x sb systems, at most the resident count
     int64_t grid = (a.n_sys + (int64_t)wpb * sb - 1) / ((int64_t)wpb * sb);
-    const int64_t cap = (int64_t)device_cu_count() * per_cu;
     if (grid > cap) grid = cap;
     if (grid < 1) grid = 1;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(block), lds, st, a, jtwr, jtwj);
@@ -500,8 +513,11 @@ hipError_t launch_gn_obs_t(DenseArgs a, double *jtwr, double *jtwj, LaunchShape 
 template <int NPL>
 hipError_t launch_gn_obs_npl(DenseArgs a, double *jtwr, double *jtwj, LaunchShape shape, hipStream_t st)
 {
-    if (a.n_obs <= 64) return launch_gn_obs_t<NPL, 1>(a, jtwr, jtwj, shape, st);
-    return launch_gn_obs_t<NPL, 2>(a, jtwr, jtwj, shape, st);
+    const int64_t need = (a.n_obs + 63) / 64;
+    if (need <= 1) return launch_gn_obs_t<NPL, 1, kOneGroup>(a, jtwr, jtwj, shape, st);
+    if (need == 2) return launch_gn_obs_t<NPL, 2, kOneGroup>(a, jtwr, jtwj, shape, st);
+    return need % 2 ? launch_gn_obs_t<NPL, 2, kOddChunks>(a, jtwr, jtwj, shape, st)
+                    : launch_gn_obs_t<NPL, 2, kGroups>(a, jtwr, jtwj, shape, st);
 }
 
 hipError_t launch_gn_mixed(DenseArgs a, double *jtwr, double *jtwj, LaunchShape shape, hipStream_t st)

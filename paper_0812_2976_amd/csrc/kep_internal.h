@@ -7,6 +7,46 @@
 
 namespace kep {
 
+// A batch of systems per wavefront (or block) and round: full rounds of `sb`
+// systems each, then one round of `sb_last` over the systems left, so that no
+// worker takes more than its share, ceil(n_sys / workers).  With every batch the
+// full one, 100,003 systems in batches of 16 on 5,120 wavefronts took two rounds,
+// the second a fifth full, and 1,048,576 took 13 for 12.8.
+struct Batches {
+    int sb, sb_last;
+    int64_t n_full;       // batches of the full rounds
+    int64_t n_batches;    // batches of both kinds: worker w takes batches w, w + workers, ...
+
+    // first system and size of batch bt
+    __host__ __device__ int64_t first(int64_t bt, int64_t n_sys, int &nb) const
+    {
+        const bool full = bt < n_full;
+        const int64_t s0 = full ? bt * sb : n_full * sb + (bt - n_full) * sb_last;
+        const int64_t left = n_sys - s0;
+        const int size = full ? sb : sb_last;
+        nb = left < size ? (int)left : size;
+        return s0;
+    }
+};
+
+// Batches of n_sys systems for `workers` wavefronts (or blocks), at most `cap`
+// systems each, in multiples of `unit` (the teams of a block).
+inline Batches make_batches(int64_t n_sys, int64_t workers, int64_t cap, int unit = 1)
+{
+    if (workers < 1) workers = 1;
+    cap = cap < unit ? unit : cap / unit * unit;
+    Batches b;
+    const int64_t full = n_sys / (workers * cap);
+    b.n_full = full * workers;
+    const int64_t left = n_sys - b.n_full * cap;
+    int64_t last = (left + workers * unit - 1) / (workers * unit) * unit;
+    if (last < unit) last = unit;
+    b.sb_last = (int)last;
+    b.sb = full > 0 ? (int)cap : b.sb_last;
+    b.n_batches = b.n_full + (left + last - 1) / last;
+    return b;
+}
+
 // Arguments of the dense kernels (observations shared by every system).
 struct DenseArgs {
     const double *t, *v, *sigma;
@@ -16,7 +56,8 @@ struct DenseArgs {
     const double *offset, *jitter;
     int64_t n_sys;
     int n_pl;
-    int sb;            // systems per setup batch of one wavefront (1..kMaxSB)
+    int sb;            // systems per setup batch of one wavefront (1..kMaxSB): bt.sb
+    Batches bt;
     double *out;       // chi2 [n_sys] or model [n_sys][n_obs]
     double *grad;      // gradient [(5 n_pl + 1 (+1 for the likelihood))][n_sys] (gradient kernels only)
     float *dv;         // per-planet velocities or eccentric anomalies [n_pl][n_sys][n_obs]
@@ -64,7 +105,8 @@ struct AstroArgs {
     const double *x0, *y0;
     int64_t n_sys;
     int n_pl;
-    int sb;
+    int sb;            // bt.sb
+    Batches bt;
     double *out;       // chi2 [n_sys] or positions [n_sys][2][n_obs]
     int fixed_iter, max_iter;
 };
@@ -145,18 +187,6 @@ hipError_t launch_demc_advance(uint64_t *gen, uint64_t inc, hipStream_t st);
 hipError_t launch_demc_half(DemcArgs m, DenseArgs base, Prec prec, int h, LaunchShape shape, hipStream_t st);
 int device_cu_count();
 
-// Systems per setup batch of a wavefront for n_sys systems over `waves` resident
-// wavefronts, at most `cap`: as many rounds of batches as the cap asks for, and
-// the smallest batch that still takes no more rounds, so that the last round is
-// as full as the others.
-inline int systems_per_batch(int64_t n_sys, int64_t waves, int64_t cap)
-{
-    if (waves < 1) waves = 1;
-    const int64_t rounds = (n_sys + waves * cap - 1) / (waves * cap);
-    const int64_t per = waves * (rounds < 1 ? 1 : rounds);
-    const int64_t sb = (n_sys + per - 1) / per;
-    return (int)(sb < 1 ? 1 : (sb > cap ? cap : sb));
-}
 
 // LDS of a block of which `blocks` share a CU: its 160 KiB are handed out in
 // pieces of 1,280 bytes (five blocks of 32,768 bytes do not fit, five of 32,000

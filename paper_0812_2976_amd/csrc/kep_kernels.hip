@@ -91,8 +91,11 @@ k_dense(DenseArgs a)
 
     const int64_t gw = (int64_t)blockIdx.x * wpb + wib;
     const int64_t n_waves = (int64_t)gridDim.x * wpb;
-    const int64_t n_batches = (a.n_sys + a.sb - 1) / a.sb;
-    const int n_groups = (int)((a.n_obs + 64 * NCH - 1) / (64 * NCH));
+    // chi-squares with the table hold every observation in one group (more go to
+    // k_dense_team); knowing it spares the group loop's registers (four chunks: 48
+    // bytes of scratch a lane with it)
+    constexpr bool kOne = MODE == kChi2 && Pol::kTables >= 1;
+    const int n_groups = kOne ? 1 : (int)((a.n_obs + 64 * NCH - 1) / (64 * NCH));
     const bool has_jit = a.jitter != nullptr;
 
     Obs o[NCH];
@@ -110,14 +113,14 @@ k_dense(DenseArgs a)
     // (batch, observation group) pairs: a few systems with very many
     // observations still spread over the whole chip.
     constexpr bool MODEL = MODE != kChi2;
-    const int64_t n_items = MODEL ? n_batches * n_groups : n_batches;
+    const int64_t n_items = MODEL ? a.bt.n_batches * n_groups : a.bt.n_batches;
     int64_t prev_bt = -1;
     for (int64_t item = gw; item < n_items; item += n_waves) {
         const int64_t bt = MODEL ? item / n_groups : item;
         const int g_first = MODEL ? (int)(item - bt * n_groups) : 0;
         const int g_end = MODEL ? g_first + 1 : n_groups;
-        const int64_t s0 = bt * a.sb;
-        const int nb = (int)min((int64_t)a.sb, a.n_sys - s0);
+        int nb;
+        const int64_t s0 = a.bt.first(bt, a.n_sys, nb);
         if (bt != prev_bt) {
         prev_bt = bt;
         wave_sync_lds();
@@ -252,7 +255,6 @@ k_dense_team(DenseArgs a, int W)
     int *sysbad = reinterpret_cast<int *>(part + (size_t)W * a.sb);
     uint32_t *tab = reinterpret_cast<uint32_t *>(smem + team_table_offset(W, a.sb, a.n_pl, sizeof(Rec)));
     double2 *knots = nullptr;
-    const int64_t n_batches = (a.n_sys + a.sb - 1) / a.sb;
     const int n_groups = (int)((a.n_obs + 64 * NCH - 1) / (64 * NCH));
     const bool has_jit = a.jitter != nullptr;
 
@@ -268,9 +270,9 @@ k_dense_team(DenseArgs a, int W)
     }
     load_start_table(tab);       // ends with the block barrier
 
-    for (int64_t bt = blockIdx.x; bt < n_batches; bt += gridDim.x) {
-        const int64_t s0 = bt * a.sb;
-        const int nb = (int)min((int64_t)a.sb, a.n_sys - s0);
+    for (int64_t bt = blockIdx.x; bt < a.bt.n_batches; bt += gridDim.x) {
+        int nb;
+        const int64_t s0 = a.bt.first(bt, a.n_sys, nb);
         __syncthreads();                                   // the previous batch's sums are written out
         for (int q = threadIdx.x; q < nb; q += blockDim.x) {
             const int64_t sys = s0 + q;
@@ -1250,9 +1252,9 @@ static hipError_t launch_dense_team(DenseArgs a, DenseSplit split, LaunchShape s
     if (per_cu <= 0) per_cu = cached_occupancy((const void *)kern, 64 * T * W, lds_of(sb_cap));
     const int64_t cap = cus * per_cu;
     // a multiple of T systems keeps the teams level
-    a.sb = T * systems_per_batch((a.n_sys + T - 1) / T, cap, sb_cap / T > 0 ? sb_cap / T : 1);
-    const int64_t n_batches = (a.n_sys + a.sb - 1) / a.sb;
-    const int64_t grid = n_batches < cap ? n_batches : cap;
+    a.bt = make_batches(a.n_sys, cap, sb_cap, T);
+    a.sb = a.bt.sb;
+    const int64_t grid = a.bt.n_batches < cap ? a.bt.n_batches : cap;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * T * W), lds_of(a.sb), st, a, W);
     return hipGetLastError();
 }
@@ -1306,11 +1308,10 @@ static hipError_t launch_dense_t(DenseArgs a, LaunchShape shape, hipStream_t st)
     if (per_cu <= 0) {
         per_cu = cached_occupancy((const void *)kern, block, lds);
     }
-    // every round as full as the others: 100,003 systems in batches of the full 16
-    // were 6,251 batches on 5,120 wavefronts, two rounds with the second a fifth full
-    a.sb = systems_per_batch(a.n_sys, (int64_t)device_cu_count() * per_cu * wpb, sb_cap);
+    a.bt = make_batches(a.n_sys, (int64_t)device_cu_count() * per_cu * wpb, sb_cap);
+    a.sb = a.bt.sb;
     lds = lds_of(a.sb);
-    const int64_t n_batches = (a.n_sys + a.sb - 1) / a.sb;
+    const int64_t n_batches = a.bt.n_batches;
     const int64_t n_groups = (a.n_obs + 64 * nch - 1) / (64 * nch);
     const int64_t n_items = MODE != kChi2 ? n_batches * (n_groups > 0 ? n_groups : 1) : n_batches;
     int64_t grid = (n_items + wpb - 1) / wpb;

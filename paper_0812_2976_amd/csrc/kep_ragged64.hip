@@ -186,7 +186,10 @@ Ragged64Shape ragged64_shape(LaunchShape shape, int64_t n_sys)
     int per_cu = shape.blocks_per_cu;
     if (per_cu <= 0) per_cu = cached_occupancy((const void *)k_ragged64<Pol>, r.block, lds_of(kRag64Batch));
     const int64_t cap = (int64_t)device_cu_count() * (per_cu > 0 ? per_cu : 1);
-    r.sb = systems_per_batch(n_sys, cap * wpb, kRag64Batch);
+    // the smallest batch that takes no more rounds than the largest would
+    const int64_t waves = cap * wpb, rounds = (n_sys + waves * kRag64Batch - 1) / (waves * kRag64Batch);
+    r.sb = (int)((n_sys + waves * rounds - 1) / (waves * (rounds > 0 ? rounds : 1)));
+    if (r.sb < 1) r.sb = 1;
     int64_t grid = ((n_sys + r.sb - 1) / r.sb + wpb - 1) / wpb;
     r.grid = (int)(grid > cap ? cap : grid < 1 ? 1 : grid);
     r.lds = lds_of(r.sb);
