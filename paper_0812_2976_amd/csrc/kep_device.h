@@ -36,11 +36,17 @@ __device__ __forceinline__ double uniform_double(double x)
 }
 
 // A binary64 value moved across lanes by a DPP pattern (both halves with the same
-// pattern; lanes of rows outside ROWS get 0).
+// pattern; lanes of rows outside ROWS get 0).  Patterns that write every lane need
+// no value for the others: without one the two zeroing moves go.
 template <int CTRL, int ROWS>
 __device__ __forceinline__ double dpp_f64(double x)
 {
     const int64_t b = __double_as_longlong(x);
+    if constexpr (ROWS == 0xf) {
+        const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffff), CTRL, 0xf, 0xf, true);
+        const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
+        return __longlong_as_double(((int64_t)hi << 32) | (uint32_t)lo);
+    }
     const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffff), CTRL, ROWS, 0xf, false);
     const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
     return __longlong_as_double(((int64_t)hi << 32) | (uint32_t)lo);

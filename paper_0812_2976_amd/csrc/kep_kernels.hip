@@ -61,7 +61,8 @@ __host__ __device__ inline size_t team_table_offset(int W, int sb, int n_pl, siz
            ~(size_t)15;
 }
 
-template <class Pol, int NCH, int MODE>
+// JIT: chi-squares with a jitter per system (other modes: false).
+template <class Pol, int NCH, int MODE, bool JIT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dense_waves_per_simd<Pol, NCH>())))
 k_dense(DenseArgs a)
 {
@@ -96,8 +97,8 @@ k_dense(DenseArgs a)
     // bytes of scratch a lane with it)
     constexpr bool kOne = MODE == kChi2 && Pol::kTables >= 1;
     const int n_groups = kOne ? 1 : (int)((a.n_obs + 64 * NCH - 1) / (64 * NCH));
-    const bool has_jit = a.jitter != nullptr;
 
+    constexpr bool MODEL = MODE != kChi2;
     Obs o[NCH];
     auto load_group = [&](int g) {
 #pragma unroll
@@ -108,11 +109,11 @@ k_dense(DenseArgs a)
         }
     };
     if (n_groups <= 1) load_group(0);
+    bool obs_bad = !MODEL && !JIT && n_groups <= 1 && __any(pol_obs_bad<Pol, NCH>(o));
 
     // Velocities need no reduction over observations, so their work items are
     // (batch, observation group) pairs: a few systems with very many
     // observations still spread over the whole chip.
-    constexpr bool MODEL = MODE != kChi2;
     const int64_t n_items = MODEL ? a.bt.n_batches * n_groups : a.bt.n_batches;
     int64_t prev_bt = -1;
     for (int64_t item = gw; item < n_items; item += n_waves) {
@@ -147,13 +148,16 @@ k_dense(DenseArgs a)
         for (int s = 0; s < nb; ++s) {
             const int64_t sys = s0 + s;
             const double gam = a.offset ? a.offset[sys] : 0.0;
-            const double jit = a.jitter ? a.jitter[sys] : 0.0;
+            const double jit = JIT ? a.jitter[sys] : 0.0;
             const bool sbad = uniform_int(sysbad[s]) != 0;
             typename Pol::ChiAcc chi;
             Pol::chi_init(chi);
             bool bad_obs = false;
             for (int g = g_first; g < g_end; ++g) {
-                if (n_groups > 1) load_group(g);
+                if (n_groups > 1) {
+                    load_group(g);
+                    if (!MODEL && !JIT) bad_obs = bad_obs || pol_obs_bad<Pol, NCH>(o);
+                }
                 if constexpr (MODE == kAnomalies) {
                     // the same solve as the velocities' (so E is the root the model uses)
                     for (int j = 0; j < a.n_pl; ++j) {
@@ -206,18 +210,12 @@ k_dense(DenseArgs a)
                         }
                     }
                 } else {
-#pragma unroll
-                    for (int c = 0; c < NCH; ++c) {
-                        if (o[c].in) {
-                            bool okw = Pol::chi_add(chi, m[c], o[c], gam, jit, has_jit);
-                            bad_obs = bad_obs || !okw || !o[c].ok;
-                        }
-                    }
+                    pol_chi_add<Pol, NCH, JIT>(chi, m, o, gam, jit, bad_obs);
                 }
             }
             if (!MODEL) {
                 double tot = wave_sum(Pol::chi_value(chi));
-                bool bad = sbad || __any(bad_obs);
+                const bool bad = sbad || obs_bad || __any(bad_obs);
                 if (lane == 0) a.out[sys] = bad ? __builtin_nan("") : tot;
             }
         }
@@ -239,7 +237,7 @@ k_dense(DenseArgs a)
 //     SIMDs idle.
 // Every observation is evaluated as by k_dense, so results differ from its only
 // in the order of the binary64 sums.
-template <class Pol, int NCH>
+template <class Pol, int NCH, bool JIT>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(dense_waves_per_simd<Pol, NCH>())))
 k_dense_team(DenseArgs a, int W)
 {
@@ -256,14 +254,17 @@ k_dense_team(DenseArgs a, int W)
     uint32_t *tab = reinterpret_cast<uint32_t *>(smem + team_table_offset(W, a.sb, a.n_pl, sizeof(Rec)));
     double2 *knots = nullptr;
     const int n_groups = (int)((a.n_obs + 64 * NCH - 1) / (64 * NCH));
-    const bool has_jit = a.jitter != nullptr;
 
     Obs o[NCH];
     auto load_group = [&](int g) {
 #pragma unroll
         for (int c = 0; c < NCH; ++c) Pol::load_obs(a, (int64_t)g * 64 * NCH + c * 64 + lane, o[c]);
     };
-    if (n_groups <= W) load_group(w);
+    bool obs_bad = false;
+    if (n_groups <= W) {
+        load_group(w);
+        obs_bad = !JIT && __any(pol_obs_bad<Pol, NCH>(o));
+    }
     if constexpr (Pol::kTables == 2) {
         knots = reinterpret_cast<double2 *>(tab + kTabWords);
         load_knots64(knots);
@@ -278,7 +279,7 @@ k_dense_team(DenseArgs a, int W)
             const int64_t sys = s0 + q;
             bool ok = isfinite(a.t0);
             if (a.offset) ok = ok && isfinite(a.offset[sys]);
-            if (has_jit) ok = ok && isfinite(a.jitter[sys]) && a.jitter[sys] >= 0.0;
+            if (JIT) ok = ok && isfinite(a.jitter[sys]) && a.jitter[sys] >= 0.0;
             sysbad[q] = ok ? 0 : 1;
         }
         __syncthreads();
@@ -292,10 +293,13 @@ k_dense_team(DenseArgs a, int W)
         __syncthreads();
 
         for (int g = w; g < n_groups; g += W) {
-            if (n_groups > W) load_group(g);
+            if (n_groups > W) {
+                load_group(g);
+                obs_bad = !JIT && __any(pol_obs_bad<Pol, NCH>(o));
+            }
             for (int s = team; s < nb; s += T) {
                 const double gam = a.offset ? a.offset[s0 + s] : 0.0;
-                const double jit = has_jit ? a.jitter[s0 + s] : 0.0;
+                const double jit = JIT ? a.jitter[s0 + s] : 0.0;
                 typename Pol::ModelAcc m[NCH];
 #pragma unroll
                 for (int c = 0; c < NCH; ++c) Pol::model_init(m[c]);
@@ -303,15 +307,9 @@ k_dense_team(DenseArgs a, int W)
                 typename Pol::ChiAcc chi;
                 Pol::chi_init(chi);
                 bool bad_obs = false;
-#pragma unroll
-                for (int c = 0; c < NCH; ++c) {
-                    if (o[c].in) {
-                        const bool okw = Pol::chi_add(chi, m[c], o[c], gam, jit, has_jit);
-                        bad_obs = bad_obs || !okw || !o[c].ok;
-                    }
-                }
+                pol_chi_add<Pol, NCH, JIT>(chi, m, o, gam, jit, bad_obs);
                 double tot = wave_sum(Pol::chi_value(chi));
-                if (__any(bad_obs)) tot = __builtin_nan("");
+                if (obs_bad || __any(bad_obs)) tot = __builtin_nan("");
                 if (lane == 0) part[w * a.sb + s] = g == w ? tot : part[w * a.sb + s] + tot;
             }
         }
@@ -1224,7 +1222,7 @@ static DenseSplit dense_split(int64_t n_sys, int n_pl, int64_t n_obs)
     return best;
 }
 
-template <class Pol>
+template <class Pol, bool JIT>
 static hipError_t launch_dense_team(DenseArgs a, DenseSplit split, LaunchShape shape, hipStream_t st)
 {
     int W = shape.block > 0 ? shape.block / 64 : split.W;
@@ -1244,10 +1242,10 @@ static hipError_t launch_dense_team(DenseArgs a, DenseSplit split, LaunchShape s
     const int blocks = 4 * dense_waves_per_simd<Pol, 4>() / (T * W);
     int64_t sb_cap = 16 * T;
     while (sb_cap > 1 && (int64_t)lds_of(sb_cap) > lds_budget(blocks > 1 ? blocks : 1)) --sb_cap;
-    void (*kern)(DenseArgs, int) = split.nch == 1   ? k_dense_team<Pol, 1>
-                                   : split.nch == 2 ? k_dense_team<Pol, 2>
-                                   : split.nch == 3 ? k_dense_team<Pol, 3>
-                                                    : k_dense_team<Pol, 4>;
+    void (*kern)(DenseArgs, int) = split.nch == 1   ? k_dense_team<Pol, 1, JIT>
+                                   : split.nch == 2 ? k_dense_team<Pol, 2, JIT>
+                                   : split.nch == 3 ? k_dense_team<Pol, 3, JIT>
+                                                    : k_dense_team<Pol, 4, JIT>;
     int per_cu = shape.blocks_per_cu;
     if (per_cu <= 0) per_cu = cached_occupancy((const void *)kern, 64 * T * W, lds_of(sb_cap));
     const int64_t cap = cus * per_cu;
@@ -1259,8 +1257,8 @@ static hipError_t launch_dense_team(DenseArgs a, DenseSplit split, LaunchShape s
     return hipGetLastError();
 }
 
-template <class Pol, int MODE>
-static hipError_t launch_dense_t(DenseArgs a, LaunchShape shape, hipStream_t st)
+template <class Pol, int MODE, bool JIT>
+static hipError_t launch_dense_jit(DenseArgs a, LaunchShape shape, hipStream_t st)
 {
     const int block = shape.block > 0 ? shape.block : 256;
     const int wpb = block / 64;
@@ -1291,18 +1289,18 @@ static hipError_t launch_dense_t(DenseArgs a, LaunchShape shape, hipStream_t st)
         nch = (int)((need + groups - 1) / groups);
         if constexpr (MODE == kChi2) {
             const DenseSplit split = dense_split(a.n_sys, a.n_pl, a.n_obs);
-            if (groups > 1 || (split.W > 1 && shape.block == 0)) return launch_dense_team<Pol>(a, split, shape, st);
+            if (groups > 1 || (split.W > 1 && shape.block == 0)) return launch_dense_team<Pol, JIT>(a, split, shape, st);
         }
-        kern = nch == 1   ? k_dense<Pol, 1, MODE>
-               : nch == 2 ? k_dense<Pol, 2, MODE>
-               : nch == 3 ? k_dense<Pol, 3, MODE>
-                          : k_dense<Pol, 4, MODE>;
+        kern = nch == 1   ? k_dense<Pol, 1, MODE, JIT>
+               : nch == 2 ? k_dense<Pol, 2, MODE, JIT>
+               : nch == 3 ? k_dense<Pol, 3, MODE, JIT>
+                          : k_dense<Pol, 4, MODE, JIT>;
     } else {
         nch = need <= 1 ? 1 : need <= 2 ? 2 : need <= 4 ? 4 : 8;
-        kern = nch == 1   ? k_dense<Pol, 1, MODE>
-               : nch == 2 ? k_dense<Pol, 2, MODE>
-               : nch == 4 ? k_dense<Pol, 4, MODE>
-                          : k_dense<Pol, 8, MODE>;
+        kern = nch == 1   ? k_dense<Pol, 1, MODE, JIT>
+               : nch == 2 ? k_dense<Pol, 2, MODE, JIT>
+               : nch == 4 ? k_dense<Pol, 4, MODE, JIT>
+                          : k_dense<Pol, 8, MODE, JIT>;
     }
     int per_cu = shape.blocks_per_cu;
     if (per_cu <= 0) {
@@ -1320,6 +1318,14 @@ static hipError_t launch_dense_t(DenseArgs a, LaunchShape shape, hipStream_t st)
     if (grid < 1) grid = 1;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(block), lds, st, a);
     return hipGetLastError();
+}
+
+template <class Pol, int MODE>
+static hipError_t launch_dense_t(DenseArgs a, LaunchShape shape, hipStream_t st)
+{
+    if constexpr (MODE == kChi2)
+        if (a.jitter) return launch_dense_jit<Pol, MODE, true>(a, shape, st);
+    return launch_dense_jit<Pol, MODE, false>(a, shape, st);
 }
 
 hipError_t launch_dense(DenseArgs a, Prec prec, bool model, LaunchShape shape, hipStream_t st)

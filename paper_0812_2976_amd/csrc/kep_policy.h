@@ -348,6 +348,16 @@ struct PolMixed {
     static __device__ __forceinline__ double model_value(const ModelAcc &m) { return m.s; }
 
     static __device__ __forceinline__ void chi_init(ChiAcc &x) { x.s = 0.0; }
+    // Without a jitter an observation's validity does not depend on the system:
+    // kernels compiled for that case test it once, at the load, and add with
+    // chi_add_plain (a test, a reciprocal and two selects fewer per observation
+    // and system, and sigma^2 not held).
+    static __device__ __forceinline__ bool obs_valid(const Obs &o) { return o.ok && o.s2 > 0.0f; }
+    static __device__ __forceinline__ void chi_add_plain(ChiAcc &x, const ModelAcc &m, const Obs &o, double gam)
+    {
+        const double r = (m.s + gam) - o.v;
+        x.s = fma((double)(o.w * (float)r), r, x.s);
+    }
     // One observation's contribution; returns false if the weight is invalid.
     static __device__ __forceinline__ bool chi_add(ChiAcc &x, const ModelAcc &m, const Obs &o, double gam,
                                                    double jit, bool has_jit)
@@ -453,6 +463,12 @@ struct Pol64 {
     static __device__ __forceinline__ void model_init(ModelAcc &m) { m.s = 0.0; }
     static __device__ __forceinline__ double model_value(const ModelAcc &m) { return m.s; }
     static __device__ __forceinline__ void chi_init(ChiAcc &x) { x = 0.0; }
+    static __device__ __forceinline__ bool obs_valid(const Obs &o) { return o.ok && o.s2 > 0.0; }
+    static __device__ __forceinline__ void chi_add_plain(ChiAcc &x, const ModelAcc &m, const Obs &o, double gam)
+    {
+        const double r = m.s + gam - o.v;
+        x = fma(o.w * r, r, x);
+    }
     static __device__ __forceinline__ bool chi_add(ChiAcc &x, const ModelAcc &m, const Obs &o, double gam,
                                                    double jit, bool has_jit)
     {
@@ -491,6 +507,35 @@ __device__ __forceinline__ void pol_add_planet(const typename Pol::Rec &r, const
 // (the paper's first mixed-precision use of the GPU, Kepler's equation only,
 // Sec. 5.2; mixed policy only).
 enum { kChi2 = 0, kModel = 1, kPlanets = 2, kAnomalies = 3 };
+
+// The chi-square terms of NCH chunks of a system's observations; JIT: with the
+// system's jitter (sets bad where a weight is invalid), else without.
+template <class Pol, int NCH, bool JIT>
+__device__ __forceinline__ void pol_chi_add(typename Pol::ChiAcc &chi, const typename Pol::ModelAcc (&m)[NCH],
+                                            const typename Pol::Obs (&o)[NCH], double gam, double jit, bool &bad)
+{
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+        if (o[c].in) {
+            if constexpr (JIT) {
+                const bool okw = Pol::chi_add(chi, m[c], o[c], gam, jit, true);
+                bad = bad || !okw || !o[c].ok;
+            } else {
+                Pol::chi_add_plain(chi, m[c], o[c], gam);
+            }
+        }
+    }
+}
+
+// Whether a lane holds an observation that no system without jitter can use.
+template <class Pol, int NCH>
+__device__ __forceinline__ bool pol_obs_bad(const typename Pol::Obs (&o)[NCH])
+{
+    bool bad = false;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) bad = bad || (o[c].in && !Pol::obs_valid(o[c]));
+    return bad;
+}
 
 
 }  // namespace kep

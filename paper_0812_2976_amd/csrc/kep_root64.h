@@ -257,6 +257,11 @@ struct Pol64R {
     static __device__ __forceinline__ void model_init(ModelAcc &m) { m.s = 0.0; }
     static __device__ __forceinline__ double model_value(const ModelAcc &m) { return m.s; }
     static __device__ __forceinline__ void chi_init(ChiAcc &x) { x = 0.0; }
+    static __device__ __forceinline__ bool obs_valid(const Obs &o) { return Pol64::obs_valid(o); }
+    static __device__ __forceinline__ void chi_add_plain(ChiAcc &x, const ModelAcc &m, const Obs &o, double gam)
+    {
+        Pol64::chi_add_plain(x, m, o, gam);
+    }
     static __device__ __forceinline__ bool chi_add(ChiAcc &x, const ModelAcc &m, const Obs &o, double gam,
                                                    double jit, bool has_jit)
     {
