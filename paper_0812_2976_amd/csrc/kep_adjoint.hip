@@ -63,8 +63,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
     int *sysbad = reinterpret_cast<int *>(smem + (size_t)wpb * a.sb * NPL * sizeof(RecGrad)) + wib * a.sb;
     uint32_t *tab = reinterpret_cast<uint32_t *>(smem + adj_table_offset(wpb, a.sb, NPL));
     double2 *knots = reinterpret_cast<double2 *>(smem + adj_knots_offset(wpb, a.sb, NPL));
+    start_table_begin(tab);
     fill_sincos64_knots(knots);
-    load_start_table(tab);          // ends with the block barrier
 
     // groups of NCH chunks, before the last one where that has fewer
     const int n_full = LAST > 0 ? (int)((a.n_obs + 64 * NCH - 1) / (64 * NCH)) - (LAST < NCH ? 1 : 0)
@@ -79,6 +79,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
         for (int c = 0; c < NCH; ++c) load_obs_g(a, (int64_t)g * 64 * NCH + c * 64 + lane, o[c]);
     };
     if (LAST == 0) load_group(0);
+    start_table_end();
 
     // batches in turn over the grid's wavefronts: the whole grid sweeps the systems in
     // order (contiguous shares per wavefront or block ran 2-7% slower: the grid then

@@ -133,10 +133,10 @@ __global__ void __launch_bounds__(256) k_astro(AstroArgs a)
     const uint32_t *tab = nullptr;
     const double2 *knots = nullptr;
     if constexpr (KIND != kAstroDanby64) {
-        __shared__ uint32_t tab_s[kTabWords];
+        __shared__ __align__(16) uint32_t tab_s[kTabWords];
         __shared__ double2 knots_s[kSc64Knots];
+        start_table_begin(tab_s);
         load_knots64(knots_s);
-        load_start_table(tab_s);        // ends with the block barrier
         tab = tab_s;
         knots = knots_s;
     }
@@ -168,6 +168,7 @@ __global__ void __launch_bounds__(256) k_astro(AstroArgs a)
         }
     };
     if (n_groups <= 1) load_group(0);
+    if constexpr (KIND != kAstroDanby64) start_table_end();
 
     const int64_t n_items = MODEL ? a.bt.n_batches * n_groups : a.bt.n_batches;
     int64_t prev_bt = -1;

@@ -68,65 +68,71 @@ DenseArgs half_dense(const DemcArgs &a, const DenseArgs &base, const double *pla
 
 // ------------------------------------------------------------------ DE-MC
 // One half-step of the population sampler, fused: for a batch of sb chains
-// of half h the wave
-//   A. lanes over chains: draw 0 gives r1 != r2 (other half) and u;
-//   B. lanes over (chain, pair of rows): two normals z and the proposal rows
+// of half h the block
+//   A. threads over chains: draw 0 gives r1 != r2 (other half) and u;
+//   B. threads over (chain, pair of rows): two normals z and the proposal rows
 //      y_r = x_ir + gam (x_r1,r - x_r2,r) + eps_r z_r;
-//   C. lanes over (chain, planet): the planet records, as the dense kernel's
+//   C. threads over (chain, planet): the planet records, as the dense kernel's
 //      setup does from parameter planes;
-//   D. lanes over chains: domain and prior-support flags;
-//   then evaluates each proposal's chi-square with the lanes over
-//   observations, exactly as the dense chi-square kernel does (in mixed
-//   precision from the block's LDS copy of the Kepler starting-value table), and
-//   E. lanes over chains: accepts iff 2 ln u < chi2(x) - chi2(y) and K >= 0,
+//   D. threads over chains: domain and prior-support flags;
+//   then evaluates each proposal's chi-square with the lanes over observations,
+//   as the dense team kernel does (T teams of W wavefronts, k_dense_team), and
+//   E. threads over chains: accepts iff 2 ln u < chi2(x) - chi2(y) and K >= 0,
 //      copying y into the chain.
-// Everything one lane hands to another goes through the wave's slice of LDS;
-// the half being updated is read and written only by the lane that owns the
-// chain in phase B / E, and the other half is only read.  The proposals and
-// their chi-square are also written to the workspace (m.y, m.c_new).
-__host__ __device__ inline size_t demc_lds_per_wave(int sb, int n_pl, int d, size_t rec_bytes)
+// Everything one thread hands to another goes through the block's LDS; the half
+// being updated is read and written only by the threads that own the chain in
+// phases B / E, and the other half is only read.  The proposals and their
+// chi-square are also written to the workspace (m.y, m.c_new).
+//
+// What bounds it: a few thousand chains are a chain of latencies (starting-value
+// table, observations, random numbers, gathers, records, solves, log u).  The
+// table arrives in LDS and the observations in registers while the proposals are
+// made; several wavefronts share a chain's observations where the population
+// leaves the chip idle otherwise.
+__host__ __device__ inline size_t demc_lds(int W, int sb, int n_pl, int d, size_t rec_bytes)
 {
     size_t b = (size_t)sb * n_pl * rec_bytes          // planet records
                + (size_t)sb * d * sizeof(double)       // proposals
-               + (size_t)sb * 2 * sizeof(double)       // u, chi2 of the proposal
+               + (size_t)sb * (1 + W) * sizeof(double) // u, each wavefront's share of the proposal's chi2
                + (size_t)sb * 2 * sizeof(uint32_t)     // r1, r2
                + (size_t)sb * n_pl * sizeof(int)       // per-planet domain flag
                + (size_t)sb * 2 * sizeof(int);         // per-chain domain and support flags
     return (b + 15) & ~(size_t)15;
 }
 
-template <class Pol, int NCH>
-__global__ void __launch_bounds__(256) k_demc_half(DenseArgs a, DemcArgs m, int h)
+template <class Pol, int NCH, bool JIT>
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4)))
+k_demc_half(DenseArgs a, DemcArgs m, int h, int W)
 {
     using Rec = typename Pol::Rec;
     using Obs = typename Pol::Obs;
     using ModelAcc = typename Pol::ModelAcc;
     extern __shared__ __align__(16) unsigned char smem[];
 
-    const int lane = __lane_id();
-    const int wpb = blockDim.x >> 6;
-    const int wib = uniform_int(threadIdx.x >> 6);
+    const int lane = __lane_id(), tid = threadIdx.x, nthr = blockDim.x;
+    const int T = uniform_int((int)(blockDim.x >> 6) / W);
+    const int team = uniform_int((int)(threadIdx.x >> 6) / W);
+    const int w = uniform_int((int)(threadIdx.x >> 6)) - team * W;
     const int sb = a.sb, npl = a.n_pl, d = m.d;
-    unsigned char *mine = smem + (size_t)wib * demc_lds_per_wave(sb, npl, d, sizeof(Rec));
-    Rec *recs = reinterpret_cast<Rec *>(mine);
-    double *y_l = reinterpret_cast<double *>(mine + (size_t)sb * npl * sizeof(Rec));
+    Rec *recs = reinterpret_cast<Rec *>(smem);
+    double *y_l = reinterpret_cast<double *>(smem + (size_t)sb * npl * sizeof(Rec));
     double *u_l = y_l + (size_t)sb * d;
-    double *cnew_l = u_l + sb;
-    uint32_t *r12_l = reinterpret_cast<uint32_t *>(cnew_l + sb);
+    double *part = u_l + sb;                              // [W][sb]
+    uint32_t *r12_l = reinterpret_cast<uint32_t *>(part + (size_t)W * sb);
     int *okpl_l = reinterpret_cast<int *>(r12_l + 2 * sb);
     int *bad_l = okpl_l + sb * npl;
     int *supp_l = bad_l + sb;
-    // the block's copies of the Kepler starting-value table and the knots after the wave slices
+    // the block's copies of the Kepler starting-value table and the knots
     const uint32_t *tab = nullptr;
     const double2 *knots = nullptr;
     if constexpr (Pol::kTables >= 1) {
-        uint32_t *t = reinterpret_cast<uint32_t *>(smem + (size_t)wpb * demc_lds_per_wave(sb, npl, d, sizeof(Rec)));
+        uint32_t *t = reinterpret_cast<uint32_t *>(smem + demc_lds(W, sb, npl, d, sizeof(Rec)));
+        start_table_begin(t);      // phase C's end waits for it
         if constexpr (Pol::kTables == 2) {
             double2 *k = reinterpret_cast<double2 *>(t + kTabWords);
             load_knots64(k);
             knots = k;
         }
-        load_start_table(t);       // ends with the block barrier
         tab = t;
     }
 
@@ -136,41 +142,39 @@ __global__ void __launch_bounds__(256) k_demc_half(DenseArgs a, DemcArgs m, int 
     double *xh = m.x + (int64_t)h * d * nh;
     const double *xo = m.x + (int64_t)(1 - h) * d * nh;
     const int ndraw = (d + 1) / 2;
-
-    const int64_t gw = (int64_t)blockIdx.x * wpb + wib;
-    const int64_t n_waves = (int64_t)gridDim.x * wpb;
     const int n_groups = (int)((a.n_obs + 64 * NCH - 1) / (64 * NCH));
-    const bool has_jit = a.jitter != nullptr;
 
     Obs o[NCH];
+    bool obs_bad = false;
     auto load_group = [&](int gi) {
 #pragma unroll
         for (int c = 0; c < NCH; ++c) Pol::load_obs(a, (int64_t)gi * 64 * NCH + c * 64 + lane, o[c]);
+        obs_bad = !JIT && __any(pol_obs_bad<Pol, NCH>(o));
     };
-    if (n_groups <= 1) load_group(0);
+    if (n_groups <= W) load_group(w);
 
-    for (int64_t bt = gw; bt < a.bt.n_batches; bt += n_waves) {
+    for (int64_t bt = blockIdx.x; bt < a.bt.n_batches; bt += gridDim.x) {
         int nb;
         const int64_t s0 = a.bt.first(bt, nh, nb);
-        wave_sync_lds();
-        for (int c = lane; c < nb; c += 64) {                                   // A
-            const U4 w = demc_draw(m.key0, m.key1, h, (uint32_t)(s0 + c), 0u, g);
-            const uint32_t r1 = below(w.w0, (uint32_t)nh);
-            uint32_t r2 = below(w.w1, (uint32_t)nh - 1u);
+        __syncthreads();
+        for (int c = tid; c < nb; c += nthr) {                                  // A
+            const U4 r = demc_draw(m.key0, m.key1, h, (uint32_t)(s0 + c), 0u, g);
+            const uint32_t r1 = below(r.w0, (uint32_t)nh);
+            uint32_t r2 = below(r.w1, (uint32_t)nh - 1u);
             if (r2 >= r1) r2 += 1u;
             r12_l[2 * c] = r1;
             r12_l[2 * c + 1] = r2;
-            u_l[c] = unit53(w.w2, w.w3);
+            u_l[c] = unit53(r.w2, r.w3);
         }
-        wave_sync_lds();
-        for (int q = lane; q < nb * ndraw; q += 64) {                           // B
+        __syncthreads();
+        for (int q = tid; q < nb * ndraw; q += nthr) {                          // B
             const int c = q / ndraw, p = q - c * ndraw, r = 2 * p;
             const int64_t i = s0 + c;
             const uint32_t r1 = r12_l[2 * c], r2 = r12_l[2 * c + 1];
-            const U4 w = demc_draw(m.key0, m.key1, h, (uint32_t)i, (uint32_t)(1 + p), g);
-            const double rho = sqrt(-2.0 * log(unit53(w.w0, w.w1)));
+            const U4 z = demc_draw(m.key0, m.key1, h, (uint32_t)i, (uint32_t)(1 + p), g);
+            const double rho = sqrt(-2.0 * log(unit53(z.w0, z.w1)));
             double sn, cs;
-            sincos(kTwoPi * unit53(w.w2, w.w3), &sn, &cs);
+            sincos(kTwoPi * unit53(z.w2, z.w3), &sn, &cs);
             {
                 // rounded term by term, as written (no contraction)
 #pragma clang fp contract(off)
@@ -186,8 +190,8 @@ __global__ void __launch_bounds__(256) k_demc_half(DenseArgs a, DemcArgs m, int 
                 }
             }
         }
-        wave_sync_lds();
-        for (int q = lane; q < nb * npl; q += 64) {                             // C
+        __syncthreads();
+        for (int q = tid; q < nb * npl; q += nthr) {                            // C
             const int c = q / npl, j = q - c * npl;
             const double *yc = y_l + c * d;
             Rec rr;
@@ -195,8 +199,9 @@ __global__ void __launch_bounds__(256) k_demc_half(DenseArgs a, DemcArgs m, int 
                             ? 1 : 0;
             recs[q] = rr;
         }
-        wave_sync_lds();
-        for (int c = lane; c < nb; c += 64) {                                   // D
+        if constexpr (Pol::kTables >= 1) start_table_end();
+        else __syncthreads();
+        for (int c = tid; c < nb; c += nthr) {                                  // D (read in phase E, by the same thread)
             const double *yc = y_l + c * d;
             bool ok = isfinite(a.t0) && isfinite(yc[5 * npl]);
             bool supp = true;
@@ -204,42 +209,39 @@ __global__ void __launch_bounds__(256) k_demc_half(DenseArgs a, DemcArgs m, int 
                 ok = ok && okpl_l[c * npl + j] != 0;
                 supp = supp && yc[npl + j] >= 0.0;
             }
-            if (has_jit) ok = ok && isfinite(a.jitter[s0 + c]) && a.jitter[s0 + c] >= 0.0;
+            if (JIT) ok = ok && isfinite(a.jitter[s0 + c]) && a.jitter[s0 + c] >= 0.0;
             bad_l[c] = ok ? 0 : 1;
             supp_l[c] = supp ? 1 : 0;
         }
-        wave_sync_lds();
 
-        for (int s = 0; s < nb; ++s) {
-            const double gam = y_l[s * d + 5 * npl];
-            const double jit = has_jit ? a.jitter[s0 + s] : 0.0;
-            const bool sbad = uniform_int(bad_l[s]) != 0;
-            typename Pol::ChiAcc chi;
-            Pol::chi_init(chi);
-            bool bad_obs = false;
-            for (int gi = 0; gi < n_groups; ++gi) {
-                if (n_groups > 1) load_group(gi);
+        for (int gi = w; gi < n_groups; gi += W) {
+            if (n_groups > W) load_group(gi);
+            for (int s = team; s < nb; s += T) {
+                const double gam = y_l[s * d + 5 * npl];
+                const double jit = JIT ? a.jitter[s0 + s] : 0.0;
                 ModelAcc mm[NCH];
 #pragma unroll
                 for (int c = 0; c < NCH; ++c) Pol::model_init(mm[c]);
                 for (int j = 0; j < npl; ++j) pol_add_planet<Pol, NCH>(recs[s * npl + j], o, mm, a, tab, knots);
-#pragma unroll
-                for (int c = 0; c < NCH; ++c) {
-                    if (o[c].in) {
-                        const bool okw = Pol::chi_add(chi, mm[c], o[c], gam, jit, has_jit);
-                        bad_obs = bad_obs || !okw || !o[c].ok;
-                    }
-                }
+                typename Pol::ChiAcc chi;
+                Pol::chi_init(chi);
+                bool bad_obs = false;
+                pol_chi_add<Pol, NCH, JIT>(chi, mm, o, gam, jit, bad_obs);
+                double tot = wave_sum(Pol::chi_value(chi));
+                if (obs_bad || __any(bad_obs)) tot = __builtin_nan("");
+                if (lane == 0) part[w * sb + s] = gi == w ? tot : part[w * sb + s] + tot;
             }
-            const double tot = wave_sum(Pol::chi_value(chi));
-            const bool bad = sbad || __any(bad_obs);
-            if (lane == 0) cnew_l[s] = bad ? __builtin_nan("") : tot;
         }
-        wave_sync_lds();
+        __syncthreads();
 
-        for (int c = lane; c < nb; c += 64) {                                   // E
+        for (int c = tid; c < nb; c += nthr) {                                  // E
             const int64_t i = s0 + c;
-            const double c_new = cnew_l[c];
+            double c_new = 0.0;
+            if (n_groups > 0) {
+                c_new = part[c];
+                for (int v = 1; v < W; ++v) c_new += part[v * sb + c];
+            }
+            if (bad_l[c] != 0) c_new = __builtin_nan("");
             double *chi = m.chi2 + (int64_t)h * nh + i;
             m.c_new[i] = c_new;
             if (supp_l[c] != 0 && 2.0 * log(u_l[c]) < *chi - c_new) {
@@ -249,39 +251,46 @@ __global__ void __launch_bounds__(256) k_demc_half(DenseArgs a, DemcArgs m, int 
             }
         }
     }
+    if constexpr (Pol::kTables >= 1)
+        if (blockIdx.x >= a.bt.n_batches) start_table_end();    // a block without a batch lets the table land
+}
+
+template <class Pol, bool JIT>
+static hipError_t launch_demc_half_t(DemcArgs m, DenseArgs a, int h, LaunchShape shape, hipStream_t st)
+{
+    // two chunks a wavefront at most: with four the registers of the proposals and of
+    // the solve together spill (2 x 32,768 chains x 4 x 256, a generation: 149 against
+    // 130 us).  Eight wavefronts share a block's tables and proposals where the
+    // population fills the chip that way (2 x 2,048: 25.4 us, four 26.7), else one team.
+    const DenseSplit split = dense_split(m.nh, a.n_pl, a.n_obs, 2);
+    const int64_t groups = (a.n_obs + 64 * split.nch - 1) / (64 * split.nch);
+    int W = shape.block > 0 ? shape.block / 64 : split.W;
+    if (W > groups) W = (int)(groups > 0 ? groups : 1);
+    const int T = shape.block > 0 ? shape.block / 64 / W
+                  : W <= 2 && m.nh >= 4 * (int64_t)device_cu_count() ? 8 / W : 1;
+    const size_t rec = sizeof(typename Pol::Rec);
+    const size_t table = (Pol::kTables >= 1 ? sizeof(kep_start_tab) : 0) + (Pol::kTables == 2 ? kSc64Bytes : 0);
+    auto lds_of = [&](int64_t sb) { return demc_lds(W, (int)sb, a.n_pl, m.d, rec) + table; };
+    // the batch leaves room for the blocks that the registers allow (four wavefronts per SIMD)
+    const int blocks = 16 / (T * W) > 8 ? 8 : 16 / (T * W);
+    int64_t sb_cap = 16 * T;
+    while (sb_cap > 1 && (int64_t)lds_of(sb_cap) > lds_budget(blocks > 1 ? blocks : 1)) --sb_cap;
+    void (*kern)(DenseArgs, DemcArgs, int, int) = split.nch == 1 ? k_demc_half<Pol, 1, JIT> : k_demc_half<Pol, 2, JIT>;
+    int per_cu = shape.blocks_per_cu;
+    if (per_cu <= 0) per_cu = cached_occupancy((const void *)kern, 64 * T * W, lds_of(sb_cap));
+    const int64_t cap = (int64_t)device_cu_count() * per_cu;
+    a.bt = make_batches(m.nh, cap, sb_cap, T);
+    a.sb = a.bt.sb;
+    const int64_t grid = a.bt.n_batches < cap ? a.bt.n_batches : cap;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * T * W), lds_of(a.sb), st, a, m, h, W);
+    return hipGetLastError();
 }
 
 template <class Pol>
-static hipError_t launch_demc_half_t(DemcArgs m, DenseArgs a, int h, LaunchShape shape, hipStream_t st)
+static hipError_t launch_demc_half_pol(DemcArgs m, DenseArgs a, int h, LaunchShape shape, hipStream_t st)
 {
-    const int block = shape.block > 0 ? shape.block : 256;
-    const int wpb = block / 64;
-    const size_t rec = sizeof(typename Pol::Rec);
-    const size_t table = (Pol::kTables >= 1 ? sizeof(kep_start_tab) : 0) + (Pol::kTables == 2 ? kSc64Bytes : 0);
-    int sb_cap = kMaxSB;
-    while (sb_cap > 1 && (size_t)wpb * demc_lds_per_wave(sb_cap, a.n_pl, m.d, rec) + table > 48 * 1024) sb_cap /= 2;
-    const int nch_needed = (int)((a.n_obs + 63) / 64);
-    void (*kern)(DenseArgs, DemcArgs, int);
-    if (nch_needed <= 1) kern = k_demc_half<Pol, 1>;
-    else if (nch_needed <= 2) kern = k_demc_half<Pol, 2>;
-    else if (nch_needed <= 4) kern = k_demc_half<Pol, 4>;
-    else if constexpr (Pol::kTables == 2) kern = k_demc_half<Pol, 4>;   // eight: 246 VGPRs
-    else kern = k_demc_half<Pol, 8>;
-    int per_cu = shape.blocks_per_cu;
-    if (per_cu <= 0) {
-        const size_t lds = (size_t)wpb * demc_lds_per_wave(sb_cap, a.n_pl, m.d, rec) + table;
-        per_cu = cached_occupancy((const void *)kern, block, lds);
-    }
-    a.bt = make_batches(m.nh, (int64_t)device_cu_count() * per_cu * wpb, sb_cap);
-    a.sb = a.bt.sb;
-    const size_t lds = (size_t)wpb * demc_lds_per_wave(a.sb, a.n_pl, m.d, rec) + table;
-    const int64_t n_batches = a.bt.n_batches;
-    int64_t grid = (n_batches + wpb - 1) / wpb;
-    const int64_t cap = (int64_t)device_cu_count() * per_cu;
-    if (grid > cap) grid = cap;
-    if (grid < 1) grid = 1;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(block), lds, st, a, m, h);
-    return hipGetLastError();
+    return a.jitter ? launch_demc_half_t<Pol, true>(m, a, h, shape, st)
+                    : launch_demc_half_t<Pol, false>(m, a, h, shape, st);
 }
 
 hipError_t launch_demc_half(DemcArgs m, DenseArgs a, Prec prec, int h, LaunchShape shape, hipStream_t st)
@@ -293,9 +302,9 @@ hipError_t launch_demc_half(DemcArgs m, DenseArgs a, Prec prec, int h, LaunchSha
     a.out = nullptr;
     a.grad = nullptr;
     a.dv = nullptr;
-    if (prec == Prec::Mixed) return launch_demc_half_t<PolMixed>(m, a, h, shape, st);
-    return a.fixed_iter == 0 ? launch_demc_half_t<Pol64R>(m, a, h, shape, st)
-                             : launch_demc_half_t<Pol64>(m, a, h, shape, st);
+    if (prec == Prec::Mixed) return launch_demc_half_pol<PolMixed>(m, a, h, shape, st);
+    return a.fixed_iter == 0 ? launch_demc_half_pol<Pol64R>(m, a, h, shape, st)
+                             : launch_demc_half_pol<Pol64>(m, a, h, shape, st);
 }
 
 hipError_t launch_demc_chisq(DemcArgs a, DenseArgs base, Prec prec, LaunchShape shape, hipStream_t st)

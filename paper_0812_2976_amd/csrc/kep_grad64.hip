@@ -79,8 +79,8 @@ k_grad64(DenseArgs a, int nll)
     if constexpr (ROOT) {
         tab = reinterpret_cast<uint32_t *>(smem + grad64_table_offset(wpb, a.sb, NPL));
         knots = reinterpret_cast<double2 *>(tab + kTabWords);
+        start_table_begin(tab);
         load_knots64(knots);
-        load_start_table(tab);          // ends with the block barrier
     }
 
     const int64_t group = 64 * NCH;
@@ -95,6 +95,7 @@ k_grad64(DenseArgs a, int nll)
         for (int c = 0; c < NCH; ++c) Pol64::load_obs(a, k0 + c * 64 + lane, o[c]);
     };
     if (a.n_obs <= group) load_group(0);
+    if constexpr (ROOT) start_table_end();
 
     // batches in turn over the grid's wavefronts: the whole grid sweeps the systems in
     // order (contiguous shares per wavefront or block ran 2-7% slower: the grid then

@@ -186,6 +186,12 @@ hipError_t launch_demc_advance(uint64_t *gen, uint64_t inc, hipStream_t st);
 // one fused half-step (propose, chi-square, accept) of half h
 hipError_t launch_demc_half(DemcArgs m, DenseArgs base, Prec prec, int h, LaunchShape shape, hipStream_t st);
 int device_cu_count();
+// How a system's observations are split (kep_kernels.hip): chunks of 64 a wavefront (at most `most`),
+// wavefronts a system.
+struct DenseSplit {
+    int nch, W;
+};
+DenseSplit dense_split(int64_t n_sys, int n_pl, int64_t n_obs, int most);
 
 
 // LDS of a block of which `blocks` share a CU: its 160 KiB are handed out in

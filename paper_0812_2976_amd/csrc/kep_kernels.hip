@@ -86,9 +86,10 @@ k_dense(DenseArgs a)
             load_knots64(k);
             knots = k;
         }
-        load_start_table(t);       // ends with the block barrier
+        start_table_begin(t);      // arrives while the observations and the first records are made
         tab = t;
     }
+    bool table_here = Pol::kTables == 0;
 
     const int64_t gw = (int64_t)blockIdx.x * wpb + wib;
     const int64_t n_waves = (int64_t)gridDim.x * wpb;
@@ -143,6 +144,10 @@ k_dense(DenseArgs a)
             recs[sq * a.n_pl + j] = r;
         }
         wave_sync_lds();
+        }
+        if (!table_here) {
+            start_table_end();     // (every wavefront passes one, here or after the loop)
+            table_here = true;
         }
 
         for (int s = 0; s < nb; ++s) {
@@ -220,6 +225,7 @@ k_dense(DenseArgs a)
             }
         }
     }
+    if (!table_here) start_table_end();
 }
 
 // Chi-square with several wavefronts over a system's observations: wavefront w of
@@ -255,6 +261,11 @@ k_dense_team(DenseArgs a, int W)
     double2 *knots = nullptr;
     const int n_groups = (int)((a.n_obs + 64 * NCH - 1) / (64 * NCH));
 
+    start_table_begin(tab);
+    if constexpr (Pol::kTables == 2) {
+        knots = reinterpret_cast<double2 *>(tab + kTabWords);
+        load_knots64(knots);
+    }
     Obs o[NCH];
     auto load_group = [&](int g) {
 #pragma unroll
@@ -265,11 +276,6 @@ k_dense_team(DenseArgs a, int W)
         load_group(w);
         obs_bad = !JIT && __any(pol_obs_bad<Pol, NCH>(o));
     }
-    if constexpr (Pol::kTables == 2) {
-        knots = reinterpret_cast<double2 *>(tab + kTabWords);
-        load_knots64(knots);
-    }
-    load_start_table(tab);       // ends with the block barrier
 
     for (int64_t bt = blockIdx.x; bt < a.bt.n_batches; bt += gridDim.x) {
         int nb;
@@ -290,7 +296,7 @@ k_dense_team(DenseArgs a, int W)
             if (!Pol::setup(a, a.P[p], a.K[p], a.e[p], a.w[p], a.M0[p], r)) sysbad[sq] = 1;
             recs[sq * a.n_pl + j] = r;
         }
-        __syncthreads();
+        start_table_end();         // (the wait is for the first batch's sake)
 
         for (int g = w; g < n_groups; g += W) {
             if (n_groups > W) {
@@ -425,15 +431,16 @@ __global__ void __launch_bounds__(256) k_kepler(const double *__restrict__ Mv, c
 {
     const uint32_t *tab = nullptr;
     const double2 *knots = nullptr;
-    if constexpr (KIND == kKepRoot64) {
-        __shared__ double2 knots_s[kSc64Knots];
-        load_knots64(knots_s);
-        knots = knots_s;
-    }
     if constexpr (KIND != kKepDanby64) {
-        __shared__ uint32_t tab_s[kTabWords];    // Kepler starting values
-        load_start_table(tab_s);                 // ends with the block barrier
+        __shared__ __align__(16) uint32_t tab_s[kTabWords];    // Kepler starting values
+        start_table_begin(tab_s);
         tab = tab_s;
+        if constexpr (KIND == kKepRoot64) {
+            __shared__ double2 knots_s[kSc64Knots];
+            load_knots64(knots_s);
+            knots = knots_s;
+        }
+        start_table_end();
     }
     const int64_t tile = (int64_t)blockDim.x * KU;
     const int64_t stride = (int64_t)gridDim.x * tile;
@@ -600,7 +607,7 @@ k_ragged_mixed(RaggedArgs a)
     // this wavefront's sums: the slice's own, or one of the block's wavefronts'
     double *acc = COOP ? reinterpret_cast<double *>(smem + ragged_lds_per_wave(sb)) + wib * sb : acc0;
     const bool has_jit = a.jitter != nullptr;
-    __shared__ uint32_t tab[kTabWords];    // Kepler starting values
+    __shared__ __align__(16) uint32_t tab[kTabWords];    // Kepler starting values
     __shared__ unsigned int drained;       // bit q: a wave of this block found queue q drained
     __shared__ unsigned int waves_out;     // the block's waves that have left the item loop
     if (threadIdx.x == 0) {
@@ -1199,22 +1206,18 @@ hipError_t launch_kepler_solve(const double *M, const double *e, double *E, int6
 // that rate.  Large batches get the NCH that fits n_obs with the fewest empty
 // chunks (157 observations: three, not four), small ones more wavefronts per
 // system.
-struct DenseSplit {
-    int nch, W;
-};
-
-static DenseSplit dense_split(int64_t n_sys, int n_pl, int64_t n_obs)
+DenseSplit dense_split(int64_t n_sys, int n_pl, int64_t n_obs, int most)
 {
     const int64_t need = n_obs > 64 ? (n_obs + 63) / 64 : 1;
     const double simds = 4.0 * device_cu_count();
-    DenseSplit best{1, 1};
+    DenseSplit best{most, 1};
     double best_cost = 0.0;
-    for (int nch = 4; nch >= 1; --nch) {
+    for (int nch = most; nch >= 1; --nch) {
         const int64_t groups = (need + nch - 1) / nch;
         const int W = (int)(groups < 16 ? groups : 16);
         const double instr = n_pl * (62.0 * nch + 25.0) + 10.0 * nch + 45.0;
         const double cost = (double)((groups + W - 1) / W) * instr * fmax(2.0, (double)n_sys * W / simds);
-        if (nch == 4 || cost < best_cost) {
+        if (nch == most || cost < best_cost) {
             best = DenseSplit{nch, W};
             best_cost = cost;
         }
@@ -1239,7 +1242,8 @@ static hipError_t launch_dense_team(DenseArgs a, DenseSplit split, LaunchShape s
     // sixteen systems a team (whole 128-byte lines of the parameter planes)
     const int64_t cus = device_cu_count();
     const int T = W <= 2 && a.n_sys >= 8 * cus ? 4 / W : 1;
-    const int blocks = 4 * dense_waves_per_simd<Pol, 4>() / (T * W);
+    int blocks = 4 * dense_waves_per_simd<Pol, 4>() / (T * W);
+    blocks = blocks > 8 ? 8 : blocks;
     int64_t sb_cap = 16 * T;
     while (sb_cap > 1 && (int64_t)lds_of(sb_cap) > lds_budget(blocks > 1 ? blocks : 1)) --sb_cap;
     void (*kern)(DenseArgs, int) = split.nch == 1   ? k_dense_team<Pol, 1, JIT>
@@ -1288,7 +1292,7 @@ static hipError_t launch_dense_jit(DenseArgs a, LaunchShape shape, hipStream_t s
         const int64_t groups = (need + 3) / 4;
         nch = (int)((need + groups - 1) / groups);
         if constexpr (MODE == kChi2) {
-            const DenseSplit split = dense_split(a.n_sys, a.n_pl, a.n_obs);
+            const DenseSplit split = dense_split(a.n_sys, a.n_pl, a.n_obs, 4);
             if (groups > 1 || (split.W > 1 && shape.block == 0)) return launch_dense_team<Pol, JIT>(a, split, shape, st);
         }
         kern = nch == 1   ? k_dense<Pol, 1, MODE, JIT>

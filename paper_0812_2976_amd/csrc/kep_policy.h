@@ -82,12 +82,35 @@ __device__ __forceinline__ TabPlace table_place(double e, bool use)
     return t;
 }
 
-// Copy of the table into a block's LDS; every thread of the block calls it
-// before any wave reads the table (it ends with the block barrier).
+// Copy of the table into a block's LDS (16-byte aligned), straight from memory:
+// every wavefront requests 16 bytes a lane into consecutive LDS, without registers
+// and without waiting.  Every thread of the block calls start_table_begin, then
+// start_table_end (which waits and ends with the block barrier) before any
+// wavefront reads the table; what stands between runs while the table arrives.
+static_assert(kTabWords % 4 == 0, "the table is copied 16 bytes at a time");
+
+__device__ __forceinline__ void start_table_begin(uint32_t *dst)
+{
+    typedef __attribute__((address_space(1))) uint32_t g_u32;
+    typedef __attribute__((address_space(3))) uint32_t l_u32;
+    const int lane = __lane_id(), nw = (int)(blockDim.x >> 6);
+    for (int q = 64 * uniform_int(threadIdx.x >> 6); q < kTabWords / 4; q += 64 * nw) {
+        if (q + lane < kTabWords / 4)
+            __builtin_amdgcn_global_load_lds((g_u32 *)(uintptr_t)(kep_start_tab + 4 * (q + lane)),
+                                             (l_u32 *)(uintptr_t)(dst + 4 * q), 16, 0, 0);
+    }
+}
+
+__device__ __forceinline__ void start_table_end()
+{
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+}
+
 __device__ __forceinline__ void load_start_table(uint32_t *dst)
 {
-    for (int q = threadIdx.x; q < kTabWords; q += blockDim.x) dst[q] = kep_start_tab[q];
-    __syncthreads();
+    start_table_begin(dst);
+    start_table_end();
 }
 
 // Knot of |M| and its fraction for mscale = knots / pi.  M is the centred phase

@@ -89,10 +89,11 @@ k_ragged64(RaggedArgs a)
     const uint32_t *tab = nullptr;
     const double2 *knots = nullptr;
     if constexpr (Pol::kTables == 2) {
-        __shared__ uint32_t tab_s[kTabWords];
+        __shared__ __align__(16) uint32_t tab_s[kTabWords];
         __shared__ double2 knots_s[kSc64Knots];
+        start_table_begin(tab_s);
         load_knots64(knots_s);
-        load_start_table(tab_s);             // ends with the block barrier
+        start_table_end();
         tab = tab_s;
         knots = knots_s;
     }
