@@ -498,9 +498,9 @@ __device__ __forceinline__ void load_unit(const RaggedArgs &a, int64_t k0, int64
 
 // One unit (the first NCH of its groups) of a system's whole groups, with the
 // lanes over its observations and uniform planet records.
-template <int NCH, int G>
+template <int NCH, int G, bool JIT>
 __device__ __forceinline__ void ragged_unit(const RaggedArgs &a, const RecMixed *recs, int npl, const RawObs<G> &r,
-                                            int64_t left, double gam, double jit, bool has_jit, PolMixed::ChiAcc &chi,
+                                            int64_t left, double gam, double jit, PolMixed::ChiAcc &chi,
                                             bool &bad_obs, const uint32_t *tab)
 {
     const int lane = __lane_id();
@@ -517,14 +517,10 @@ __device__ __forceinline__ void ragged_unit(const RaggedArgs &a, const RecMixed 
     PolMixed::ModelAcc m[NCH];
 #pragma unroll
     for (int c = 0; c < NCH; ++c) PolMixed::model_init(m[c]);
+    // (before the planets, so that sigma^2 need not be held for them)
+    if constexpr (!JIT) bad_obs = bad_obs || pol_obs_bad<PolMixed, NCH>(o);
     for (int j = 0; j < npl; ++j) PolMixed::add_planet<NCH>(recs[j], o, m, a.max_iter, 0, tab);
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        if (o[c].in) {
-            bool okw = PolMixed::chi_add(chi, m[c], o[c], gam, jit, has_jit);
-            bad_obs = bad_obs || !okw || !o[c].ok;
-        }
-    }
+    pol_chi_add<PolMixed, NCH, JIT>(chi, m, o, gam, jit, bad_obs);
 }
 
 // One planet's velocity (the arithmetic of PolMixed::add_planet) from this
@@ -577,7 +573,7 @@ __device__ __forceinline__ int64_t uniform_i64(int64_t x)
 // items), where one wavefront per item left most of the chip idle for as long as
 // the largest item takes.  The evaluations are the same: units, and groups of 64
 // tail lanes, hold the same observations in either form.
-template <int GMAX, bool COOP>
+template <int GMAX, bool COOP, bool JIT>
 __global__ void __launch_bounds__(COOP ? 1024 : 256) __attribute__((amdgpu_waves_per_eu(GMAX == 2 ? 5 : 4)))
 k_ragged_mixed(RaggedArgs a)
 {
@@ -606,7 +602,6 @@ k_ragged_mixed(RaggedArgs a)
     int *bad = tpre + sb + 1;
     // this wavefront's sums: the slice's own, or one of the block's wavefronts'
     double *acc = COOP ? reinterpret_cast<double *>(smem + ragged_lds_per_wave(sb)) + wib * sb : acc0;
-    const bool has_jit = a.jitter != nullptr;
     __shared__ __align__(16) uint32_t tab[kTabWords];    // Kepler starting values
     __shared__ unsigned int drained;       // bit q: a wave of this block found queue q drained
     __shared__ unsigned int waves_out;     // the block's waves that have left the item loop
@@ -677,7 +672,7 @@ k_ragged_mixed(RaggedArgs a)
                 // the system's offset and jitter with its offsets, not behind the
                 // planet parameters (one dependent round trip fewer per item)
                 gj[2 * lane] = a.offset ? a.offset[sys] : 0.0;
-                gj[2 * lane + 1] = a.jitter ? a.jitter[sys] : 0.0;
+                gj[2 * lane + 1] = JIT ? a.jitter[sys] : 0.0;
                 meta[2 * lane] = (int)(a.pl_off[sys + 1] - p0);
                 meta[2 * lane + 1] = (int)sys;
                 pofs[lane] = p0;
@@ -731,7 +726,7 @@ k_ragged_mixed(RaggedArgs a)
                 if (j < npl) ok = ok && okpl[lane * kMaxPl + j] != 0;
             const double g = gj[2 * lane], sj = gj[2 * lane + 1];
             if (a.offset) ok = ok && isfinite(g);
-            if (a.jitter) ok = ok && isfinite(sj) && sj >= 0.0;
+            if (JIT) ok = ok && isfinite(sj) && sj >= 0.0;
             meta[2 * lane] = ok ? npl : -npl;
         }
         sync_item();
@@ -769,11 +764,11 @@ k_ragged_mixed(RaggedArgs a)
                 const int code = uniform_int(meta[2 * us]);
                 const double gam = gj[2 * us], jit = gj[2 * us + 1];
                 const RecMixed *rs = recs + us * kMaxPl;
-                if (left <= 64) ragged_unit<1, GMAX>(a, rs, code, cur, left, gam, jit, has_jit, chi, bad_obs, tab);
+                if (left <= 64) ragged_unit<1, GMAX, JIT>(a, rs, code, cur, left, gam, jit, chi, bad_obs, tab);
                 else if (GMAX == 2 || left <= 128)
-                    ragged_unit<2, GMAX>(a, rs, code, cur, left, gam, jit, has_jit, chi, bad_obs, tab);
-                else if (left <= 192) ragged_unit<3, GMAX>(a, rs, code, cur, left, gam, jit, has_jit, chi, bad_obs, tab);
-                else ragged_unit<GMAX, GMAX>(a, rs, code, cur, left, gam, jit, has_jit, chi, bad_obs, tab);
+                    ragged_unit<2, GMAX, JIT>(a, rs, code, cur, left, gam, jit, chi, bad_obs, tab);
+                else if (left <= 192) ragged_unit<3, GMAX, JIT>(a, rs, code, cur, left, gam, jit, chi, bad_obs, tab);
+                else ragged_unit<GMAX, GMAX, JIT>(a, rs, code, cur, left, gam, jit, chi, bad_obs, tab);
                 }
                 if (ns != us) {
                     const double tot = wave_sum(PolMixed::chi_value(chi));
@@ -845,9 +840,15 @@ k_ragged_mixed(RaggedArgs a)
                     const double gam = gj[2 * sc], jit = gj[2 * sc + 1];
                     PolMixed::ChiAcc cx;
                     PolMixed::chi_init(cx);
-                    const bool okw = PolMixed::chi_add(cx, m, o, gam, jit, has_jit);
+                    bool okw;
+                    if constexpr (JIT) {
+                        okw = PolMixed::chi_add(cx, m, o, gam, jit, true) && o.ok;
+                    } else {
+                        okw = PolMixed::obs_valid(o);
+                        PolMixed::chi_add_plain(cx, m, o, gam);
+                    }
                     x = PolMixed::chi_value(cx);
-                    if (!okw || !o.ok) bad[sc] = 1;     // every writer stores the same value
+                    if (!okw) bad[sc] = 1;              // every writer stores the same value
                 }
                 // segmented scan: a lane adds only partial sums that start inside
                 // its own system's run of lanes (from `head`), so the lane that
@@ -1089,10 +1090,11 @@ static hipError_t launch_ragged_coop(RaggedArgs a, LaunchShape shape, hipStream_
     const int block = shape.block > 0 ? shape.block : a.n_items <= 2 * (int64_t)device_cu_count() ? 512 : 256;
     const size_t lds = ragged_coop_lds(block, a.sb);
     int per_cu = shape.blocks_per_cu;
-    if (per_cu <= 0) per_cu = cached_occupancy((const void *)k_ragged_mixed<2, true>, block, lds);
+    void (*kern)(RaggedArgs) = a.jitter ? k_ragged_mixed<2, true, true> : k_ragged_mixed<2, true, false>;
+    if (per_cu <= 0) per_cu = cached_occupancy((const void *)kern, block, lds);
     const int64_t cap = (int64_t)device_cu_count() * per_cu;
     const int grid = (int)(a.n_items < cap ? a.n_items : cap);
-    hipLaunchKernelGGL((k_ragged_mixed<2, true>), dim3(grid), dim3(block), lds, st, a);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(block), lds, st, a);
     return hipGetLastError();
 }
 
@@ -1400,7 +1402,7 @@ int ragged_max_grid(LaunchShape shape, int sb, int gmax)
     const int block = shape.block > 0 ? shape.block : 256;
     int per_cu = shape.blocks_per_cu;
     if (per_cu <= 0) {
-        void (*kern)(RaggedArgs) = gmax == 2 ? k_ragged_mixed<2, false> : k_ragged_mixed<4, false>;
+        void (*kern)(RaggedArgs) = gmax == 2 ? k_ragged_mixed<2, false, true> : k_ragged_mixed<4, false, true>;
         per_cu = cached_occupancy((const void *)kern, block, ragged_lds(block, sb));
     }
     return device_cu_count() * per_cu;
@@ -1409,10 +1411,9 @@ int ragged_max_grid(LaunchShape shape, int sb, int gmax)
 hipError_t launch_ragged(RaggedArgs a, LaunchShape shape, int grid, hipStream_t st)
 {
     const int block = shape.block > 0 ? shape.block : 256;
-    if (a.gmax == 2)
-        hipLaunchKernelGGL((k_ragged_mixed<2, false>), dim3(grid > 0 ? grid : 1), dim3(block), ragged_lds(block, a.sb), st, a);
-    else
-        hipLaunchKernelGGL((k_ragged_mixed<4, false>), dim3(grid > 0 ? grid : 1), dim3(block), ragged_lds(block, a.sb), st, a);
+    void (*kern)(RaggedArgs) = a.gmax == 2 ? (a.jitter ? k_ragged_mixed<2, false, true> : k_ragged_mixed<2, false, false>)
+                                           : (a.jitter ? k_ragged_mixed<4, false, true> : k_ragged_mixed<4, false, false>);
+    hipLaunchKernelGGL(kern, dim3(grid > 0 ? grid : 1), dim3(block), ragged_lds(block, a.sb), st, a);
     return hipGetLastError();
 }
 
