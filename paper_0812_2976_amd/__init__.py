@@ -24,6 +24,7 @@ fastest); observations are 1-D float64 CUDA tensors.
 """
 import ctypes
 import os
+import struct
 
 import torch
 
@@ -97,6 +98,15 @@ class KeplerError(RuntimeError):
 
 
 _LIB = None
+_FAST = {}                 # entry points that take the packed structures below, set by load_library
+
+# kep_obs, kep_params, kep_astro_obs and kep_astro_params as bytes: packing a
+# structure costs a fifth of filling a ctypes one (a call on a handful of systems
+# is bound by this module, 13 us with a 5 us kernel).
+_OBS = struct.Struct("QQQqd").pack
+_PAR = struct.Struct("QQQQQQQqq").pack
+_ASTRO_OBS = struct.Struct("QQQQQqd").pack
+_ASTRO_PAR = struct.Struct("QQQQQQQQQqq").pack
 
 EXPORTS = ("kepler_solve", "rv_model", "rv_chisq", "rv_chisq_grad", "rv_nll_grad", "rv_chisq_gn", "rv_planet_velocities",
            "rv_chisq_from_velocities", "rv_eccentric_anomalies", "kep_plan_ragged", "rv_chisq_ragged", "rv_chisq_ragged_direct",
@@ -149,6 +159,15 @@ def load_library(path: str = LIB_PATH):
                  "kep_plan_get_info", "demc_chisq", "demc_generations", "kep_plan_demc", "demc_run",
                  "astro_model", "astro_chisq"):
         getattr(L, name).restype = ctypes.c_int
+    # the same functions with their structures as bytes
+    n, i = _D, ctypes.c_int
+    for name, pointers in (("rv_model", 1), ("rv_chisq", 1), ("rv_chisq_grad", 2), ("rv_nll_grad", 2), ("rv_chisq_gn", 3),
+                           ("astro_model", 1), ("astro_chisq", 1), ("rv_planet_velocities", 0),
+                           ("rv_eccentric_anomalies", 0)):
+        f = L[name]                     # a function object of its own
+        f.argtypes = [n, n] + ([n] * pointers + [i] if pointers else [n]) + [P(KepOptions), n]
+        f.restype = i
+        _FAST[name] = f
     _LIB = L
     return L
 
@@ -201,9 +220,9 @@ def _opt_dev(x, name, n):
 def _out(x, name, shape, device, dtype=torch.float64):
     """A result tensor: allocated when None, else checked to be a contiguous GPU
     tensor of exactly `shape` (the kernels write through its pointer)."""
-    shape = tuple(int(n) for n in shape)
     if x is None:
         return torch.empty(shape, dtype=dtype, device=device)
+    shape = tuple(int(n) for n in shape)
     if not isinstance(x, torch.Tensor) or not x.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
     if x.dtype != dtype or tuple(x.shape) != shape or not x.is_contiguous():
@@ -218,8 +237,41 @@ def _ptr(x):
     return None if x is None else x.data_ptr()
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device):
+    if _raw_stream is not None:         # the handle alone, without building a Stream object
+        return _raw_stream(device.index)
     return torch.cuda.current_stream(device).cuda_stream
+
+
+_T, _F64 = torch.Tensor, torch.float64
+
+
+def _plain_vectors(n, *xs):
+    """Whether every x is None or a contiguous float64 GPU vector of n elements."""
+    for x in xs:
+        if x is not None and not (type(x) is _T and x.is_cuda and x.dtype is _F64 and x.is_contiguous() and
+                                  x.dim() == 1 and x.numel() == n):
+            return False
+    return True
+
+
+def _plain_planes(*xs):
+    """The common shape of contiguous float64 GPU planes (n_pl, n_sys), or None."""
+    x = xs[0]
+    if type(x) is not _T:
+        return None
+    shape = x.shape
+    for x in xs:
+        if not (type(x) is _T and x.is_cuda and x.dtype is _F64 and x.is_contiguous() and x.shape == shape):
+            return None
+    return shape if len(shape) == 2 else None
+
+
+def _ptr0(x):
+    return 0 if x is None else x.data_ptr()
 
 
 def _planes(P, K, e, omega, M0):
@@ -245,29 +297,36 @@ def kepler_solve(M, e, prec="mixed", out=None, opts=None):
 
 
 def _obs_params(t, v, sigma, P, K, e, omega, M0, offset, jitter, t0):
-    P, K, e, omega, M0 = _planes(P, K, e, omega, M0)
-    n_pl, n_sys = P.shape
-    t = _dev(t, "t", 1)
-    v = None if v is None else _dev(v, "v", 1)
-    sigma = None if sigma is None else _dev(sigma, "sigma", 1)
-    for x, nm in ((v, "v"), (sigma, "sigma")):
-        if x is not None and x.numel() != t.numel():
-            raise ValueError(f"{nm} must have n_obs = {t.numel()} elements")
-    offset = _opt_dev(offset, "offset", n_sys)
-    jitter = _opt_dev(jitter, "jitter", n_sys)
-    obs = KepObs(t.data_ptr(), _ptr(v), _ptr(sigma), t.numel(), float(t0))
-    par = KepParams(P.data_ptr(), K.data_ptr(), e.data_ptr(), omega.data_ptr(), M0.data_ptr(), _ptr(offset),
-                    _ptr(jitter), n_sys, n_pl)
-    keep = (t, v, sigma, P, K, e, omega, M0, offset, jitter)
-    return obs, par, keep, t.device
+    """Packed kep_obs and kep_params, (n_pl, n_sys, n_obs), the device, and the tensors to hold for the call."""
+    shape = _plain_planes(P, K, e, omega, M0)
+    n_obs = t.numel() if type(t) is _T else -1
+    if shape is None or not _plain_vectors(n_obs, t, v, sigma) or t is None or \
+            not _plain_vectors(shape[1], offset, jitter):
+        # anything else: checked one by one, made contiguous, or refused
+        P, K, e, omega, M0 = _planes(P, K, e, omega, M0)
+        shape = P.shape
+        t = _dev(t, "t", 1)
+        n_obs = t.numel()
+        v = None if v is None else _dev(v, "v", 1)
+        sigma = None if sigma is None else _dev(sigma, "sigma", 1)
+        for x, nm in ((v, "v"), (sigma, "sigma")):
+            if x is not None and x.numel() != n_obs:
+                raise ValueError(f"{nm} must have n_obs = {n_obs} elements")
+        offset = _opt_dev(offset, "offset", shape[1])
+        jitter = _opt_dev(jitter, "jitter", shape[1])
+    n_pl, n_sys = shape
+    obs = _OBS(t.data_ptr(), _ptr0(v), _ptr0(sigma), n_obs, float(t0))
+    par = _PAR(P.data_ptr(), K.data_ptr(), e.data_ptr(), omega.data_ptr(), M0.data_ptr(), _ptr0(offset),
+               _ptr0(jitter), n_sys, n_pl)
+    return obs, par, (n_pl, n_sys, n_obs), t.device, (t, v, sigma, P, K, e, omega, M0, offset, jitter)
 
 
 def rv_model(t, P, K, e, omega, M0, offset=None, t0=0.0, prec="mixed", out=None, opts=None):
     """Model velocities (n_sys, n_obs): sum over planets of the Keplerian velocity plus offset."""
-    obs, par, keep, dev = _obs_params(t, None, None, P, K, e, omega, M0, offset, None, t0)
-    out = _out(out, "out", (par.n_sys, obs.n_obs), dev)
-    L = load_library()
-    _check(L.rv_model(ctypes.byref(obs), ctypes.byref(par), out.data_ptr(), _prec(prec), _opts(opts), _stream(dev)))
+    load_library()
+    obs, par, (_, n_sys, n_obs), dev, keep = _obs_params(t, None, None, P, K, e, omega, M0, offset, None, t0)
+    out = _out(out, "out", (n_sys, n_obs), dev)
+    _check(_FAST["rv_model"](obs, par, out.data_ptr(), _prec(prec), _opts(opts), _stream(dev)))
     return out
 
 
@@ -277,22 +336,22 @@ def rv_chisq(t, v, sigma, P, K, e, omega, M0, offset=None, jitter=None, t0=0.0, 
     P, K, e, omega, M0 are planes of shape (n_pl, n_sys). Parameters held
     system-major, (n_sys, n_pl), are passed as their transposed views (`P.T`); every
     entry point copies a non-contiguous argument into a contiguous plane first."""
-    obs, par, keep, dev = _obs_params(t, v, sigma, P, K, e, omega, M0, offset, jitter, t0)
-    out = _out(out, "out", (par.n_sys,), dev)
-    L = load_library()
-    _check(L.rv_chisq(ctypes.byref(obs), ctypes.byref(par), out.data_ptr(), _prec(prec), _opts(opts), _stream(dev)))
+    load_library()
+    obs, par, (_, n_sys, _), dev, keep = _obs_params(t, v, sigma, P, K, e, omega, M0, offset, jitter, t0)
+    out = _out(out, "out", (n_sys,), dev)
+    _check(_FAST["rv_chisq"](obs, par, out.data_ptr(), _prec(prec), _opts(opts), _stream(dev)))
     return out
 
 
 def rv_chisq_grad(t, v, sigma, P, K, e, omega, M0, offset=None, jitter=None, t0=0.0, prec="mixed",
                   out=None, grad=None, opts=None):
     """(chi2 (n_sys,), grad (5 n_pl + 1, n_sys)); rows P, K, e, omega, M0 per planet, then offset."""
-    obs, par, keep, dev = _obs_params(t, v, sigma, P, K, e, omega, M0, offset, jitter, t0)
-    out = _out(out, "out", (par.n_sys,), dev)
-    grad = _out(grad, "grad", (5 * par.n_pl + 1, par.n_sys), dev)
-    L = load_library()
-    _check(L.rv_chisq_grad(ctypes.byref(obs), ctypes.byref(par), out.data_ptr(), grad.data_ptr(), _prec(prec),
-                           _opts(opts), _stream(dev)))
+    load_library()
+    obs, par, (n_pl, n_sys, _), dev, keep = _obs_params(t, v, sigma, P, K, e, omega, M0, offset, jitter, t0)
+    out = _out(out, "out", (n_sys,), dev)
+    grad = _out(grad, "grad", (5 * n_pl + 1, n_sys), dev)
+    _check(_FAST["rv_chisq_grad"](obs, par, out.data_ptr(), grad.data_ptr(), _prec(prec), _opts(opts),
+                                  _stream(dev)))
     return out, grad
 
 
@@ -301,12 +360,12 @@ def rv_nll_grad(t, v, sigma, P, K, e, omega, M0, offset=None, jitter=None, t0=0.
     """(nll (n_sys,), grad (5 n_pl + 2, n_sys)): nll = chi2 + sum_k ln(sigma_k^2 + s^2)
     (= -2 ln L without the n_obs ln 2 pi constant); rows P, K, e, omega, M0 per
     planet, then offset, then jitter."""
-    obs, par, keep, dev = _obs_params(t, v, sigma, P, K, e, omega, M0, offset, jitter, t0)
-    out = _out(out, "out", (par.n_sys,), dev)
-    grad = _out(grad, "grad", (5 * par.n_pl + 2, par.n_sys), dev)
-    L = load_library()
-    _check(L.rv_nll_grad(ctypes.byref(obs), ctypes.byref(par), out.data_ptr(), grad.data_ptr(), _prec(prec),
-                         _opts(opts), _stream(dev)))
+    load_library()
+    obs, par, (n_pl, n_sys, _), dev, keep = _obs_params(t, v, sigma, P, K, e, omega, M0, offset, jitter, t0)
+    out = _out(out, "out", (n_sys,), dev)
+    grad = _out(grad, "grad", (5 * n_pl + 2, n_sys), dev)
+    _check(_FAST["rv_nll_grad"](obs, par, out.data_ptr(), grad.data_ptr(), _prec(prec), _opts(opts),
+                                _stream(dev)))
     return out, grad
 
 
@@ -315,33 +374,34 @@ def rv_chisq_gn(t, v, sigma, P, K, e, omega, M0, offset=None, jitter=None, t0=0.
     """Gauss-Newton products: (chi2 (n_sys,), J^T W r (np, n_sys), J^T W J packed upper
     triangle (np (np + 1) / 2, n_sys)), np = 5 n_pl + 1, entry (a, b), a <= b, at row
     a np - a (a - 1) / 2 + (b - a)."""
-    obs, par, keep, dev = _obs_params(t, v, sigma, P, K, e, omega, M0, offset, jitter, t0)
-    npar = 5 * par.n_pl + 1
-    out = _out(out, "out", (par.n_sys,), dev)
-    jtwr = _out(jtwr, "jtwr", (npar, par.n_sys), dev)
-    jtwj = _out(jtwj, "jtwj", (npar * (npar + 1) // 2, par.n_sys), dev)
-    _check(load_library().rv_chisq_gn(ctypes.byref(obs), ctypes.byref(par), out.data_ptr(), jtwr.data_ptr(),
-                                      jtwj.data_ptr(), _prec(prec), _opts(opts), _stream(dev)))
+    load_library()
+    obs, par, (n_pl, n_sys, _), dev, keep = _obs_params(t, v, sigma, P, K, e, omega, M0, offset, jitter, t0)
+    npar = 5 * n_pl + 1
+    out = _out(out, "out", (n_sys,), dev)
+    jtwr = _out(jtwr, "jtwr", (npar, n_sys), dev)
+    jtwj = _out(jtwj, "jtwj", (npar * (npar + 1) // 2, n_sys), dev)
+    _check(_FAST["rv_chisq_gn"](obs, par, out.data_ptr(), jtwr.data_ptr(), jtwj.data_ptr(), _prec(prec), _opts(opts),
+                                _stream(dev)))
     return out, jtwr, jtwj
 
 
 def rv_planet_velocities(t, P, K, e, omega, M0, t0=0.0, out=None, opts=None):
     """Every planet's velocity (n_pl, n_sys, n_obs) in binary32, mixed precision
     (first kernel of the paper's separate-function form)."""
-    obs, par, keep, dev = _obs_params(t, None, None, P, K, e, omega, M0, None, None, t0)
-    out = _out(out, "out", (par.n_pl, par.n_sys, obs.n_obs), dev, torch.float32)
-    _check(load_library().rv_planet_velocities(ctypes.byref(obs), ctypes.byref(par), out.data_ptr(), _opts(opts),
-                                               _stream(dev)))
+    load_library()
+    obs, par, shape, dev, keep = _obs_params(t, None, None, P, K, e, omega, M0, None, None, t0)
+    out = _out(out, "out", shape, dev, torch.float32)
+    _check(_FAST["rv_planet_velocities"](obs, par, out.data_ptr(), _opts(opts), _stream(dev)))
     return out
 
 
 def rv_eccentric_anomalies(t, P, K, e, omega, M0, t0=0.0, out=None, opts=None):
     """Every planet's eccentric anomaly (n_pl, n_sys, n_obs) in binary32, in [-pi, pi]
     (Kepler's equation only, mixed precision)."""
-    obs, par, keep, dev = _obs_params(t, None, None, P, K, e, omega, M0, None, None, t0)
-    out = _out(out, "out", (par.n_pl, par.n_sys, obs.n_obs), dev, torch.float32)
-    _check(load_library().rv_eccentric_anomalies(ctypes.byref(obs), ctypes.byref(par), out.data_ptr(), _opts(opts),
-                                                 _stream(dev)))
+    load_library()
+    obs, par, shape, dev, keep = _obs_params(t, None, None, P, K, e, omega, M0, None, None, t0)
+    out = _out(out, "out", shape, dev, torch.float32)
+    _check(_FAST["rv_eccentric_anomalies"](obs, par, out.data_ptr(), _opts(opts), _stream(dev)))
     return out
 
 
@@ -364,42 +424,48 @@ def rv_chisq_from_velocities(t, v, sigma, dv, offset=None, jitter=None, t0=0.0, 
 
 
 def _astro(t, x, y, sigma_x, sigma_y, P, e, M0, A, B, F, G, x0, y0, t0):
-    planes = [_dev(a, n, 2) for a, n in zip((P, e, M0, A, B, F, G), ("P", "e", "M0", "A", "B", "F", "G"))]
-    shape = planes[0].shape
-    if any(p.shape != shape for p in planes):
-        raise ValueError("P, e, M0, A, B, F, G must share the shape (n_pl, n_sys)")
-    n_pl, n_sys = shape
-    t = _dev(t, "t", 1)
-    obs_arrays = []
-    for arr, nm in ((x, "x"), (y, "y"), (sigma_x, "sigma_x"), (sigma_y, "sigma_y")):
-        arr = None if arr is None else _dev(arr, nm, 1)
-        if arr is not None and arr.numel() != t.numel():
-            raise ValueError(f"{nm} must have n_obs = {t.numel()} elements")
-        obs_arrays.append(arr)
-    x0 = _opt_dev(x0, "x0", n_sys)
-    y0 = _opt_dev(y0, "y0", n_sys)
-    obs = KepAstroObs(t.data_ptr(), *[_ptr(a) for a in obs_arrays], t.numel(), float(t0))
-    par = KepAstroParams(*[p.data_ptr() for p in planes], _ptr(x0), _ptr(y0), n_sys, n_pl)
-    return obs, par, (t, obs_arrays, planes, x0, y0), t.device
+    """Packed kep_astro_obs and kep_astro_params, (n_sys, n_obs), the device, and the tensors to hold."""
+    planes, arrays = (P, e, M0, A, B, F, G), (x, y, sigma_x, sigma_y)
+    shape = _plain_planes(*planes)
+    n_obs = t.numel() if type(t) is _T else -1
+    if shape is None or not _plain_vectors(n_obs, t, *arrays) or t is None or not _plain_vectors(shape[1], x0, y0):
+        planes = [_dev(a, n, 2) for a, n in zip(planes, ("P", "e", "M0", "A", "B", "F", "G"))]
+        shape = planes[0].shape
+        if any(p.shape != shape for p in planes):
+            raise ValueError("P, e, M0, A, B, F, G must share the shape (n_pl, n_sys)")
+        t = _dev(t, "t", 1)
+        n_obs = t.numel()
+        checked = []
+        for arr, nm in zip(arrays, ("x", "y", "sigma_x", "sigma_y")):
+            arr = None if arr is None else _dev(arr, nm, 1)
+            if arr is not None and arr.numel() != n_obs:
+                raise ValueError(f"{nm} must have n_obs = {n_obs} elements")
+            checked.append(arr)
+        arrays = checked
+        x0 = _opt_dev(x0, "x0", shape[1])
+        y0 = _opt_dev(y0, "y0", shape[1])
+    obs = _ASTRO_OBS(t.data_ptr(), *[_ptr0(a) for a in arrays], n_obs, float(t0))
+    par = _ASTRO_PAR(*[p.data_ptr() for p in planes], _ptr0(x0), _ptr0(y0), shape[1], shape[0])
+    return obs, par, (shape[1], n_obs), t.device, (t, arrays, planes, x0, y0)
 
 
 def astro_model(t, P, e, M0, A, B, F, G, x0=None, y0=None, t0=0.0, prec="mixed", out=None, opts=None):
     """Astrometric model offsets (n_sys, 2, n_obs): row 0 dRA* = B X + G Y (+ x0), row 1
     dDec = A X + F Y (+ y0), X = cos E - e, Y = sqrt(1 - e^2) sin E."""
-    obs, par, keep, dev = _astro(t, None, None, None, None, P, e, M0, A, B, F, G, x0, y0, t0)
-    out = _out(out, "out", (par.n_sys, 2, obs.n_obs), dev)
-    _check(load_library().astro_model(ctypes.byref(obs), ctypes.byref(par), out.data_ptr(), _prec(prec),
-                                      _opts(opts), _stream(dev)))
+    load_library()
+    obs, par, (n_sys, n_obs), dev, keep = _astro(t, None, None, None, None, P, e, M0, A, B, F, G, x0, y0, t0)
+    out = _out(out, "out", (n_sys, 2, n_obs), dev)
+    _check(_FAST["astro_model"](obs, par, out.data_ptr(), _prec(prec), _opts(opts), _stream(dev)))
     return out
 
 
 def astro_chisq(t, x, y, sigma_x, sigma_y, P, e, M0, A, B, F, G, x0=None, y0=None, t0=0.0, prec="mixed",
                 out=None, opts=None):
     """chi-square per system of the astrometric model against offsets (x, y)."""
-    obs, par, keep, dev = _astro(t, x, y, sigma_x, sigma_y, P, e, M0, A, B, F, G, x0, y0, t0)
-    out = _out(out, "out", (par.n_sys,), dev)
-    _check(load_library().astro_chisq(ctypes.byref(obs), ctypes.byref(par), out.data_ptr(), _prec(prec),
-                                      _opts(opts), _stream(dev)))
+    load_library()
+    obs, par, (n_sys, _), dev, keep = _astro(t, x, y, sigma_x, sigma_y, P, e, M0, A, B, F, G, x0, y0, t0)
+    out = _out(out, "out", (n_sys,), dev)
+    _check(_FAST["astro_chisq"](obs, par, out.data_ptr(), _prec(prec), _opts(opts), _stream(dev)))
     return out
 
 
