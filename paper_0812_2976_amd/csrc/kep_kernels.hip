@@ -1239,11 +1239,12 @@ static hipError_t launch_dense_team(DenseArgs a, DenseSplit split, LaunchShape s
     // teams per block: four wavefronts share the tables (two teams of two: one team
     // left no room for records, 60,000 x 4 x 300 256 us against 152; two teams of
     // three, six wavefronts on four SIMDs, 30,000 x 4 x 700 228 against 162), unless
-    // the systems do not fill the chip that way.  Systems per batch: the blocks that the
+    // the systems do not fill the chip that way or the caller's blocks are smaller.
+    // Systems per batch: the blocks that the
     // registers allow (four or five wavefronts per SIMD) share a CU's LDS, at most
     // sixteen systems a team (whole 128-byte lines of the parameter planes)
     const int64_t cus = device_cu_count();
-    const int T = W <= 2 && a.n_sys >= 8 * cus ? 4 / W : 1;
+    const int T = W <= 2 && (shape.block > 0 ? shape.block >= 256 : a.n_sys >= 8 * cus) ? 4 / W : 1;
     int blocks = 4 * dense_waves_per_simd<Pol, 4>() / (T * W);
     blocks = blocks > 8 ? 8 : blocks;
     int64_t sb_cap = 16 * T;
