@@ -381,7 +381,7 @@ def main():
     peak = mix_peak_ops_per_s(classes) / 1e12
     roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": round(peak, 3), "unit": "TOP/s",
                 "frac": round(achieved / peak, 4), "traffic": recorded_traffic("rv_chisq_mixed_c2"),
-                "kernel": "k_dense<PolMixed,4,0>", "ops_per_triple": round(ops / triples, 2),
+                "kernel": "k_dense<PolMixed,4,0,false>", "ops_per_triple": round(ops / triples, 2),
                 "ops_per_triple_by_class": {c: round(n, 3) for c, n in classes.items()},
                 "peak_basis": "per SIMD and cycle: 32 binary32, 16 binary64, 8 transcendental lane operations; "
                               "1024 SIMDs at 2.4 GHz",
@@ -459,7 +459,7 @@ def main():
                                      "system"),
                                  "kepler_only": {"launch_ms": mse, "solves_per_s": dv.numel() / (mse * 1e-3),
                                                  "roofline": hbm_roofline(
-                                                     "k_dense<PolMixed,4,3>", dv_bytes + wl.n_sys * wl.n_pl * 40, mse,
+                                                     "k_dense<PolMixed,4,3,false>", dv_bytes + wl.n_sys * wl.n_pl * 40, mse,
                                                      "binary32 E written (n_pl x n_sys x n_obs x 4 B) + parameters "
                                                      "40 B per planet read"),
                                                  "written_GB": dv_bytes / 1e9,
@@ -494,7 +494,7 @@ def main():
         nch4 = 1 if w4.t.size <= 64 else (2 if (w4.n_pl > 4 or w4.t.size <= 128) else 4)
         result["gradient_c4"] = {"chi2_grad_per_s": w4.n_sys / (msg * 1e-3), "launch_ms": msg,
                                  "triples_per_s": tri4 / (msg * 1e-3),
-                                 "roofline": roofline_entry(f"k_grad_obs<{w4.n_pl},{nch4}>",
+                                 "roofline": roofline_entry(f"k_grad_obs<{w4.n_pl},{nch4},0>",
                                                             adjoint_op_classes(w4.n_pl, nch4, halley_fraction(0.8)),
                                                             tri4, msg,
                                                             recorded_traffic("rv_chisq_grad_mixed_c4", ADJOINT_FILES)),
@@ -571,7 +571,7 @@ def main():
                                "fp64_launch_ms": msr64, "speedup_vs_fp64": msr64 / msr_direct,
                                "kepler_solves_per_s": info["triples"] / (msr_direct * 1e-3),
                                "triples": info["triples"],
-                               "roofline": roofline_entry(f"k_ragged_mixed<{info['group_chunks']}>", cls3, tri3,
+                               "roofline": roofline_entry(f"k_ragged_mixed<{info['group_chunks']},false,false>", cls3, tri3,
                                                           msr_direct, recorded_traffic("rv_chisq_ragged_c3")),
                                "hbm_GBps_algorithmic": (obs3 * 24 + int(rw.pl_off[-1]) * 40 + rw.n_sys * 24)
                                                        / (msr_direct * 1e-3) / 1e9,
@@ -680,7 +680,7 @@ def main():
         n = M.size
         result["kepler_solve"] = {"n": n, "mixed_solves_per_s": n / (msk * 1e-3), "mixed_launch_ms": msk,
                                   "mixed_hbm_GBps": 24 * n / (msk * 1e-3) / 1e9,
-                                  "roofline": hbm_roofline("k_kepler<true,4>", 24 * n, msk,
+                                  "roofline": hbm_roofline("k_kepler<1,4>", 24 * n, msk,
                                                            "M and e read, E written: 8 B each per pair"),
                                   "fp64_solves_per_s": n / (msk64 * 1e-3), "fp64_launch_ms": msk64}
         del Mg, eg, Eg

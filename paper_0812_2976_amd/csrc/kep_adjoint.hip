@@ -9,7 +9,10 @@
 // batch), the eccentricity schedule is uniform.  Three wavefronts per SIMD
 // (up to 168 VGPRs): at four the compiler spilled up to 220 bytes per lane,
 // and the spill slots' write-backs tripled the kernel's HBM writes for the
-// same time; at three at most 56 bytes remain (four planets, four chunks).
+// same time; at three at most 8 bytes remain (four planets, four chunks; 56 in
+// the form that also streams further groups, LAST > 0).  Bound by VALU issue:
+// 262,144 x 4 x 256 1.12 ms with one form for every n_obs, 1.09 with the single
+// group's own; 60,000 x 3 x 170 208 -> 166 us with three chunks instead of four.
 // Per group of observations:
 //   pass 1, per planet: binary64 phase, binary32 Kepler solve (table start or
 //     schedule), binary64 correction of E and binary64 velocity (kep_grad.h);

@@ -12,7 +12,10 @@
 //
 // Mapping as in the dense RV kernels: one wavefront per system at a time with
 // the lanes over observations (NCH register chunks), per-planet constants
-// built with the lanes over systems and handed over through LDS.
+// built with the lanes over a batch's systems or (planet, system) pairs and
+// handed over through LDS.  Bound by VALU issue: 200,000 x 2 x 128 mixed 213 ->
+// 198 us; binary64 100,000 x 2 x 128 3.2 ms by thirty steps, 0.12 ms by the
+// corrected root.
 #include <hip/hip_runtime.h>
 
 #include "kep_device.h"
@@ -120,9 +123,19 @@ __device__ __forceinline__ void astro_cs_f64(const AstroRec &r, double tt, int f
 }
 
 template <int KIND, int NCH, bool MODEL>
-__global__ void __launch_bounds__(256) k_astro(AstroArgs a)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KIND == kAstroMixed && NCH <= 2 ? 5 : 1)))
+k_astro(AstroArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
+    // One or two chunks are never empty: without a branch around each, two solves run
+    // side by side (100,003 x 3 x 100: 148 -> 138 us, binary64 187 -> 168; held to five
+    // wavefronts per SIMD, without which 300,000 x 1 x 128 ran 196 against 187).  Of four
+    // chunks the last group's may be, and are passed over.
+    constexpr bool kWhole = NCH <= 2;
+    // Planet records with the lanes over the batch's (planet, system) pairs (60,000 x 5 x
+    // 128: 146 -> 128 us); in the four-chunk mixed kernel, whose batches hold few systems
+    // for their work, over the systems (its loop of groups ran 6% slower behind the pairs)
+    constexpr bool kPairs = NCH <= 2 || KIND != kAstroMixed;
     const int lane = __lane_id();
     const int wpb = blockDim.x >> 6;
     const int wib = uniform_int(threadIdx.x >> 6);
@@ -153,6 +166,7 @@ __global__ void __launch_bounds__(256) k_astro(AstroArgs a)
             const int64_t k = (int64_t)g * 64 * NCH + c * 64 + lane;
             o[c].in = k < a.n_obs;
             o[c].ok = true;
+            if (kWhole) o[c].t = a.t0;      // lanes past the end are solved too
             if (!o[c].in) continue;
             o[c].t = a.t[k];
             o[c].ok = isfinite(o[c].t);
@@ -184,16 +198,27 @@ __global__ void __launch_bounds__(256) k_astro(AstroArgs a)
             if (lane < nb) {
                 const int64_t sys = s0 + lane;
                 bool ok = isfinite(a.t0);
-                for (int j = 0; j < npl; ++j) {
-                    AstroRec r;
-                    ok = astro_setup<KIND>(a, (int64_t)j * a.n_sys + sys, r) && ok;
-                    recs[lane * npl + j] = r;
+                if constexpr (!kPairs) {
+                    for (int j = 0; j < npl; ++j) {
+                        AstroRec r;
+                        ok = astro_setup<KIND>(a, (int64_t)j * a.n_sys + sys, r) && ok;
+                        recs[lane * npl + j] = r;
+                    }
                 }
                 if (a.x0) ok = ok && isfinite(a.x0[sys]);
                 if (a.y0) ok = ok && isfinite(a.y0[sys]);
                 sysbad[lane] = ok ? 0 : 1;
             }
             wave_sync_lds();
+            if constexpr (kPairs) {
+                for (int q = lane; q < nb * npl; q += 64) {
+                    const int j = q / nb, sq = q - j * nb;
+                    AstroRec r;
+                    if (!astro_setup<KIND>(a, (int64_t)j * a.n_sys + s0 + sq, r)) sysbad[sq] = 1;
+                    recs[sq * npl + j] = r;
+                }
+                wave_sync_lds();
+            }
         }
         for (int s = 0; s < nb; ++s) {
             const int64_t sys = s0 + s;
@@ -210,7 +235,7 @@ __global__ void __launch_bounds__(256) k_astro(AstroArgs a)
                     const AstroRec &r = recs[s * npl + j];
 #pragma unroll
                     for (int c = 0; c < NCH; ++c) {
-                        if (!o[c].in) continue;
+                        if (!kWhole && !o[c].in) continue;
                         double cE, sE;
                         if (KIND == kAstroMixed) astro_cs_mixed(r, o[c].t - a.t0, a.max_iter, tab, knots, cE, sE);
                         else astro_cs_f64<KIND>(r, o[c].t - a.t0, fixed, a.max_iter, tab, knots, cE, sE);

@@ -6,9 +6,9 @@
 // for the whole launch), so every parameter a lane needs is wave-uniform and
 // the eccentricity schedule of the Kepler solve is uniform across the wave.
 // Per-planet constants (reciprocal period, phase offset, amplitudes) are
-// computed with the lanes spread over systems instead -- one lane per system
-// for a batch of up to 32 systems -- and handed over through the wave's slice
-// of LDS, so that setup is paid once per system rather than once per lane.
+// computed with the lanes spread over a batch's (planet, system) pairs instead
+// and handed over through the wave's slice of LDS, so that setup is paid once
+// per system rather than once per lane.
 // The chi-square is reduced across the wave in binary64 (Sec. 4.4's final sum).
 #include <hip/hip_runtime.h>
 
@@ -27,10 +27,11 @@ namespace kep {
 // to four chunks per lane are held to five wavefronts per SIMD (at most 102
 // VGPRs).  With four chunks the compiler would otherwise use 126 VGPRs (four
 // wavefronts); the extra wavefront lets the SIMD issue binary32 arithmetic
-// from more wavefronts at once.  At five the four-chunk chi-square keeps 52
-// bytes per lane in scratch (its HBM traffic 1.38 of the algorithmic bytes);
-// held to four wavefronts it has none but ran 4% slower (c2 1.757 against
-// 1.688 ms).
+// from more wavefronts at once: 4% (1,048,576 x 4 x 256, 1.757 against 1.688 ms,
+// when the jitter's and the further groups' registers put 52 bytes per lane in
+// scratch).  Compiled without them (JIT, the one group that a launch without
+// teams has) the four-chunk chi-square keeps 12 bytes there and takes 1.535 ms.
+// It issues vector instructions for nearly all of that time.
 template <class Pol, int NCH>
 constexpr int dense_waves_per_simd()
 {
@@ -242,7 +243,10 @@ k_dense(DenseArgs a)
 //   - few systems: a system's observations one wavefront after another leave most
 //     SIMDs idle.
 // Every observation is evaluated as by k_dense, so results differ from its only
-// in the order of the binary64 sums.
+// in the order of the binary64 sums.  Before and after: 60,000 x 4 x 300 257 ->
+// 152 us, 30,000 x 4 x 700 262 -> 164, 5,000 x 2 x 5,000 169 -> 105; few systems,
+// bound by the launch and one pass of dependent work: 1 x 4 x 1,000 17.4 -> 8.3,
+// 16 x 4 x 300 12.4 -> 7.6.
 template <class Pol, int NCH, bool JIT>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(dense_waves_per_simd<Pol, NCH>())))
 k_dense_team(DenseArgs a, int W)
@@ -563,7 +567,7 @@ __device__ __forceinline__ int64_t uniform_i64(int64_t x)
 // GMAX: largest observation group in 64-lane chunks (2 or 4): fewer chunks in
 // flight need fewer registers and allow more resident waves; the plan's
 // autotuner picks it.  Five wavefronts per SIMD with two chunks (96 VGPRs, 16
-// bytes of scratch), four with four (128 VGPRs, 68 bytes): at c3 the four-chunk
+// bytes of scratch), four with four (128 VGPRs, 72 bytes): at c3 the four-chunk
 // form at four wavefronts runs 3% faster than the two-chunk one at four.
 //
 // COOP: a block takes an item, not a wavefront: its wavefronts build the item's
@@ -1240,9 +1244,9 @@ static hipError_t launch_dense_team(DenseArgs a, DenseSplit split, LaunchShape s
     // left no room for records, 60,000 x 4 x 300 256 us against 152; two teams of
     // three, six wavefronts on four SIMDs, 30,000 x 4 x 700 228 against 162), unless
     // the systems do not fill the chip that way or the caller's blocks are smaller.
-    // Systems per batch: the blocks that the
-    // registers allow (four or five wavefronts per SIMD) share a CU's LDS, at most
-    // sixteen systems a team (whole 128-byte lines of the parameter planes)
+    // Systems per batch: the blocks that the registers allow (four or five
+    // wavefronts per SIMD) share a CU's LDS, at most sixteen systems a team (whole
+    // 128-byte lines of the parameter planes)
     const int64_t cus = device_cu_count();
     const int T = W <= 2 && (shape.block > 0 ? shape.block >= 256 : a.n_sys >= 8 * cus) ? 4 / W : 1;
     int blocks = 4 * dense_waves_per_simd<Pol, 4>() / (T * W);

@@ -7,6 +7,7 @@ import torch
 
 import oracle
 import paper_0812_2976_amd as kp
+import synth
 from tests import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -59,3 +60,23 @@ def test_every_system_once(n_sys):
         ab = [x * 0.1 for x in par[1:2]] * 4
         kp.astro_chisq(t, v, v, s, s, par[0], par[2], par[4], *ab, prec=prec, out=out)
         assert torch.all(out == out[0]), prec
+
+
+@pytest.mark.parametrize("n_sys,n_pl,n_obs", [(20000, 8, 3), (20000, 8, 65), (9000, 7, 128), (1, 1, 1), (40000, 1, 64)])
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+def test_astrometry_records(n_sys, n_pl, n_obs, prec):
+    """Records built over (planet, system) pairs, more than 64 of them in a one-wavefront block, and chunks
+    whose last lanes are past the end: a system's result does not depend on the batch it is in."""
+    wl = synth.astro(n_sys=n_sys, n_pl=n_pl, n_obs=n_obs, e_range=(0.0, 0.95))
+    obs = {k: torch.as_tensor(x, device="cuda") for k, x in
+           dict(t=wl.t, x=wl.noise_x, y=wl.noise_y, sigma_x=wl.sx, sigma_y=wl.sy).items()}
+    cols = {k: torch.as_tensor(getattr(wl, k), device="cuda") for k in ("P", "e", "M0", "A", "B", "F", "G", "x0", "y0")}
+    chi2 = kp.astro_chisq(**obs, **cols, prec=prec)
+    assert torch.isfinite(chi2).all()
+    assert torch.equal(chi2, kp.astro_chisq(**obs, **cols, prec=prec, opts={"block_threads": 64}))
+    few = {k: x[..., -5:].contiguous() for k, x in cols.items()}
+    assert torch.equal(chi2[-5:], kp.astro_chisq(**obs, **few, prec=prec))
+    cols["G"][n_pl - 1, n_sys // 2] = float("nan")
+    bad = kp.astro_chisq(**obs, **cols, prec=prec)
+    keep = torch.arange(n_sys, device="cuda") != n_sys // 2
+    assert torch.isnan(bad[n_sys // 2]) and torch.equal(bad[keep], chi2[keep])
