@@ -90,7 +90,6 @@ k_dense(DenseArgs a)
         start_table_begin(t);      // arrives while the observations and the first records are made
         tab = t;
     }
-    bool table_here = Pol::kTables == 0;
 
     const int64_t gw = (int64_t)blockIdx.x * wpb + wib;
     const int64_t n_waves = (int64_t)gridDim.x * wpb;
@@ -118,14 +117,7 @@ k_dense(DenseArgs a)
     // observations still spread over the whole chip.
     const int64_t n_items = MODEL ? a.bt.n_batches * n_groups : a.bt.n_batches;
     int64_t prev_bt = -1;
-    for (int64_t item = gw; item < n_items; item += n_waves) {
-        const int64_t bt = MODEL ? item / n_groups : item;
-        const int g_first = MODEL ? (int)(item - bt * n_groups) : 0;
-        const int g_end = MODEL ? g_first + 1 : n_groups;
-        int nb;
-        const int64_t s0 = a.bt.first(bt, a.n_sys, nb);
-        if (bt != prev_bt) {
-        prev_bt = bt;
+    auto make_batch = [&](int64_t s0, int nb) {
         wave_sync_lds();
         if (lane < nb) {
             const int64_t sys = s0 + lane;
@@ -145,9 +137,35 @@ k_dense(DenseArgs a)
             recs[sq * a.n_pl + j] = r;
         }
         wave_sync_lds();
+    };
+    // The first records are made while the table arrives.  The kernels that write
+    // velocities wait for it before the loop, where the wait is passed once: inside,
+    // their LDS reads also waited for the stores of the systems before (models of
+    // 1,048,576 x 4 x 256 1.68 against 1.55 ms).  The chi-square has no such stores
+    // and one copy of the setup in its code (1.54 against 1.61 ms with two).
+    bool table_here = Pol::kTables == 0;
+    if constexpr (MODEL && Pol::kTables >= 1) {
+        if (gw < n_items) {
+            int nb;
+            prev_bt = gw / n_groups;
+            const int64_t s0 = a.bt.first(prev_bt, a.n_sys, nb);
+            make_batch(s0, nb);
         }
-        if (!table_here) {
-            start_table_end();     // (every wavefront passes one, here or after the loop)
+        start_table_end();
+        table_here = true;
+    }
+    for (int64_t item = gw; item < n_items; item += n_waves) {
+        const int64_t bt = MODEL ? item / n_groups : item;
+        const int g_first = MODEL ? (int)(item - bt * n_groups) : 0;
+        const int g_end = MODEL ? g_first + 1 : n_groups;
+        int nb;
+        const int64_t s0 = a.bt.first(bt, a.n_sys, nb);
+        if (bt != prev_bt) {
+            prev_bt = bt;
+            make_batch(s0, nb);
+        }
+        if (!MODEL && !table_here) {
+            start_table_end_uncounted();     // (every wavefront passes one, here or after the loop)
             table_here = true;
         }
 
@@ -226,7 +244,7 @@ k_dense(DenseArgs a)
             }
         }
     }
-    if (!table_here) start_table_end();
+    if (!table_here) start_table_end_uncounted();
 }
 
 // Chi-square with several wavefronts over a system's observations: wavefront w of
@@ -1317,11 +1335,23 @@ static hipError_t launch_dense_jit(DenseArgs a, LaunchShape shape, hipStream_t s
     if (per_cu <= 0) {
         per_cu = cached_occupancy((const void *)kern, block, lds);
     }
-    a.bt = make_batches(a.n_sys, (int64_t)device_cu_count() * per_cu * wpb, sb_cap);
+    const int64_t n_groups = (a.n_obs + 64 * nch - 1) / (64 * nch);
+    const int64_t workers = (int64_t)device_cu_count() * per_cu * wpb;
+    a.bt = make_batches(a.n_sys, workers, sb_cap);
+    if (MODE != kChi2) {
+        // equal batches, an item for each of a batch's groups: what bounds these is the
+        // streaming of their results, which a partly filled last round does not slow,
+        // while a round of smaller batches sets up more often (400,000 x 2 x 128
+        // anomalies 142 against 136 us)
+        const int64_t share = workers / (n_groups > 0 ? n_groups : 1), w = share > 0 ? share : 1;
+        int64_t sb = (a.n_sys + w - 1) / w;
+        sb = sb < 1 ? 1 : sb > sb_cap ? sb_cap : sb;
+        const int64_t n = (a.n_sys + sb - 1) / sb;
+        a.bt = Batches{(int)sb, (int)sb, n, n};
+    }
     a.sb = a.bt.sb;
     lds = lds_of(a.sb);
     const int64_t n_batches = a.bt.n_batches;
-    const int64_t n_groups = (a.n_obs + 64 * nch - 1) / (64 * nch);
     const int64_t n_items = MODE != kChi2 ? n_batches * (n_groups > 0 ? n_groups : 1) : n_batches;
     int64_t grid = (n_items + wpb - 1) / wpb;
     const int64_t cap = (int64_t)device_cu_count() * per_cu;

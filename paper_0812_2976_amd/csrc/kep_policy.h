@@ -101,7 +101,19 @@ __device__ __forceinline__ void start_table_begin(uint32_t *dst)
     }
 }
 
+// (The wait is the builtin, which the compiler counts: behind a wait that it does not
+// see it takes the copy to be in flight still, and waits again, for every store in
+// flight too, at each later read of LDS.)
 __device__ __forceinline__ void start_table_end()
+{
+    __asm__ volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0f70);       // vmcnt(0)
+    __syncthreads();
+}
+
+// The same with a wait that the compiler does not count, for the one-store loop of the
+// dense chi-square: 1,048,576 x 4 x 256 1.535 ms, 1.55 with the counted one.
+__device__ __forceinline__ void start_table_end_uncounted()
 {
     __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
