@@ -334,6 +334,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
             const int64_t p = (int64_t)j * a.n_sys + first + (int64_t)wpb * sq;
             RecGrad r;
             if (!grad_setup_rec(a.fixed_iter, a.P[p], a.K[p], a.e[p], a.w[p], a.M0[p], r)) sysbad[sq] = 1;
+            // the column factors 2 pi K/P and K as the binary32 pair that the rows use
+            r.fP = __hiloint2double(__float_as_int((float)r.fK), __float_as_int((float)r.fP));
             recs[sq * NPL + j] = r;
         }
         wave_sync_lds();
@@ -400,9 +402,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
                         const RecGrad &rr = rs[j];
                         float x[5];
                         grad_terms_ce(rr, sE[j][c], cme[j][c], (float)(o[c].tt * rr.ph.rP), x);
-                        const float fK = (float)rr.fK;
+                        const double f = rr.fP;
+                        const float fP = __int_as_float(__double2loint(f)), fK = __int_as_float(__double2hiint(f));
                         float *cj = col + 5 * j * kGnCol;
-                        cj[0 * kGnCol] = sw * ((float)rr.fP * x[0]);
+                        cj[0 * kGnCol] = sw * (fP * x[0]);
                         cj[1 * kGnCol] = sw * x[1];
                         cj[2 * kGnCol] = sw * (fK * x[2]);
                         cj[3 * kGnCol] = -sw * (fK * x[3]);
