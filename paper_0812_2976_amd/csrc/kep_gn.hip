@@ -334,7 +334,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
             const int64_t p = (int64_t)j * a.n_sys + first + (int64_t)wpb * sq;
             RecGrad r;
             if (!grad_setup_rec(a.fixed_iter, a.P[p], a.K[p], a.e[p], a.w[p], a.M0[p], r)) sysbad[sq] = 1;
-            // the column factors 2 pi K/P and K as the binary32 pair that the rows use
+            // the column factors 2 pi K/P and K as the binary32 pair that the rows use (read as
+            // binary64 and converted for every chunk: 262,144 x 4 x 256 1.83 against 1.81 ms)
             r.fP = __hiloint2double(__float_as_int((float)r.fK), __float_as_int((float)r.fP));
             recs[sq * NPL + j] = r;
         }
