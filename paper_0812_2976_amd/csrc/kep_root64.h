@@ -149,20 +149,37 @@ __device__ __forceinline__ void refine_root64(double e, float E32, double M, boo
     r.rD = rcp64_refine(r.D, far ? (double)rcp32((float)r.D) : rD);
 }
 
+// The largest |M| that counts as centred: pi and more than any rounding of it, and
+// short of the knot after pi (the starting-value table has one word past it).
+constexpr double kCentred = 3.1416;
+
+// An angle less the multiple of 2 pi nearest to it (2 pi in two parts), for every
+// finite angle: one subtraction leaves |x| <= pi + |x| 2^-51, so it is repeated until
+// x is centred (one subtraction below 1e10, two at 1e17, twenty at 1e308; per record,
+// not per observation).  The table's index has no other bound: with one subtraction
+// here and one in mean_anomaly64c it left its row from |M0| ~ 1e31.
+__host__ __device__ __forceinline__ double centre_angle(double x)
+{
+    do {
+        const double n = rint(x * kInvTwoPi);
+        x = fma(-n, kTwoPiLo, fma(-n, kTwoPiHi, x));
+    } while (fabs(x) > kCentred);
+    return x;
+}
+
 // Per-planet constants of the centred binary64 mean anomaly.
 struct Phase64c {
     double P, rP;   // rP = 1/P correctly rounded; NaN where it overflows (P below 2^-1024)
     double M0c;     // M0 reduced to [-pi, pi]
 };
 
-__device__ __forceinline__ Phase64c make_phase64c(double P, double M0)
+__host__ __device__ __forceinline__ Phase64c make_phase64c(double P, double M0)
 {
     Phase64c p;
     p.P = P;
     const double rP = 1.0 / P;
     p.rP = rP <= 1.7976931348623157e308 ? rP : __builtin_nan("");
-    const double n = rint(M0 * kInvTwoPi);
-    p.M0c = fma(-n, kTwoPiLo, fma(-n, kTwoPiHi, M0));
+    p.M0c = centre_angle(M0);
     return p;
 }
 
@@ -172,7 +189,7 @@ __device__ __forceinline__ Phase64c make_phase64c(double P, double M0)
 // where 1/P overflows), q less its nearest integer exactly, 2 pi times it plus
 // M0 in one fused multiply-add, reduced once more with 2 pi in two parts.
 // Each rounding is at a magnitude of at most 2 pi (4 pi before centring).
-__device__ __forceinline__ double mean_anomaly64c(double tt, const Phase64c &p, double &q)
+__host__ __device__ __forceinline__ double mean_anomaly64c(double tt, const Phase64c &p, double &q)
 {
     if (p.rP == p.rP) {
         const double q0 = tt * p.rP;
