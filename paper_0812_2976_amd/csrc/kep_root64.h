@@ -167,6 +167,22 @@ __host__ __device__ __forceinline__ double centre_angle(double x)
     return x;
 }
 
+// A mean anomaly as r + 2 pi (k + k2), |M| < 2^54: r centred, k its whole turns as the
+// product with 1/(2 pi) rounds them, k2 those that this rounding missed (M of 3.7e14
+// next to an odd multiple of pi gave r = -3.169, a knot past its row).  k is exact and
+// so is its product with either part of 2 pi.
+__host__ __device__ __forceinline__ double centre_turns(double M, double &k, double &k2)
+{
+    k = rint(M * kInvTwoPi);
+    double r = fma(-k, kTwoPiLo, fma(-k, kTwoPiHi, M));
+    k2 = 0.0;
+    if (fabs(r) > kCentred) {
+        k2 = rint(r * kInvTwoPi);
+        r = fma(-k2, kTwoPiLo, fma(-k2, kTwoPiHi, r));
+    }
+    return r;
+}
+
 // Per-planet constants of the centred binary64 mean anomaly.
 struct Phase64c {
     double P, rP;   // rP = 1/P correctly rounded; NaN where it overflows (P below 2^-1024)

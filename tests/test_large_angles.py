@@ -1,6 +1,7 @@
-"""The binary64 path's reduction of angles, compiled for the host from the kernels' own
-header (no GPU): for every finite M0 the mean anomaly of Eq. 4 lies in [-pi, pi], so the
-knot that the Kepler solve reads from the starting-value table lies in its row."""
+"""The reduction of angles, compiled for the host from the kernels' own header (no GPU):
+for every finite M0 the mean anomaly of Eq. 4 lies in [-pi, pi], and so does what the
+standalone solve leaves of M, so the knot that the Kepler solve reads from the
+starting-value table lies in its row."""
 import ctypes
 import math
 import os
@@ -23,6 +24,10 @@ extern "C" void phases(const double *tt, const double *P, const double *M0, long
         M0c[i] = p.M0c;
         M[i] = kep::mean_anomaly64c(tt[i], p, q);
     }
+}
+extern "C" void turns(const double *M, long n, double *r, double *k, double *k2)
+{
+    for (long i = 0; i < n; ++i) r[i] = kep::centre_turns(M[i], k[i], k2[i]);
 }
 """
 
@@ -86,3 +91,21 @@ def test_m0_is_reduced_modulo_two_pi(host):
             r = mp.mpf(x) - mp.mpf(c)
             r -= 2 * mp.pi * mp.nint(r / (2 * mp.pi))
             assert abs(r) <= 4 * math.pi * 2.0 ** -53 + abs(x) * 2.0 ** -105, x
+
+
+@pytest.mark.parametrize("lo,hi", [(-300, 0), (0, 4), (4, 12), (12, 15), (15, 16.2556)])
+def test_standalone_mean_anomaly_is_centred(host, lo, hi):
+    """|M| < 2^54: r lies in [-pi, pi], k + k2 are the whole turns, and r + 2 pi (k + k2) is M to two
+    roundings at the magnitude of r and 2^-107 (the second part of 2 pi) a turn."""
+    M = _angles(np.random.default_rng(int(lo) + 400), lo, hi, 20000)
+    if lo == 12:
+        M = np.append(M, 367531048600891.44)
+    M = M[np.abs(M) < 2.0 ** 54]
+    r, k, k2 = _call(host.turns, (M,), 3)
+    assert np.abs(r).max() <= math.pi + 2.0 ** -17
+    for j, last in _knots(r):
+        assert j.min() >= 0 and j.max() <= last
+    assert np.array_equal(k, np.rint(k)) and np.array_equal(k2, np.rint(k2)) and (k2[np.abs(M) < 1e10] == 0).all()
+    with mp.workdps(60):
+        for x, y, n in zip(M[::40], r[::40], (k + k2)[::40]):
+            assert abs(mp.mpf(x) - mp.mpf(y) - 2 * mp.pi * mp.mpf(n)) <= 4 * math.pi * 2.0 ** -53 + abs(x) * 2.0 ** -105, x
