@@ -143,7 +143,8 @@ __device__ __forceinline__ void refine_root64(double e, float E32, double M, boo
     r.E = E0 + d;
     r.s = fma(c, d, fma(-s, od, s));
     r.c = fma(-s, d, fma(-c, od, c));
-    if (__any(far)) danby_finish64(e, M, far, knots, r);
+    // (a NaN stays as it is: the steps' clamps would make a number of it)
+    if (__any(far)) danby_finish64(e, M, far && M == M, knots, r);
     r.D = fma(-e, r.c, 1.0);
     // D at E and at E + d differ by a relative ~1e-6 at most, unless steps followed
     r.rD = rcp64_refine(r.D, far ? (double)rcp32((float)r.D) : rD);
