@@ -151,7 +151,9 @@ k_gn64(DenseArgs a, double *jtwr, double *jtwj)
                 const double swK = sw * p.K;
                 model += p.K * dvdK;
                 double *cj = col + 5 * j * kGn64Col;
-                cj[0 * kGn64Col] = swK * x[0] * (kTwoPi * q[0] * (p.ph.rP == p.ph.rP ? p.ph.rP : 1.0 / p.ph.P));
+                // (where 1/P overflows q may be 0: at the epoch, and past the last observation)
+                const double qP = kTwoPi * q[0];
+                cj[0 * kGn64Col] = swK * x[0] * (p.ph.rP == p.ph.rP ? qP * p.ph.rP : qP / p.ph.P);
                 cj[1 * kGn64Col] = sw * dvdK;
                 cj[2 * kGn64Col] = swK * x[1];
                 cj[3 * kGn64Col] = -swK * x[2];

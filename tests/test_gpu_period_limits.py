@@ -1,5 +1,6 @@
 """Binary64 entry points at periods near the ends of binary64: where (t - t0)/P
-overflows the result is NaN at every eccentricity."""
+overflows the result is NaN at every eccentricity, and at the epoch itself, where the
+phase is M0/(2 pi) for every period, values and derivatives are finite."""
 import numpy as np
 import pytest
 import torch
@@ -41,3 +42,19 @@ def test_overflowing_phase_is_nan(e):
     s.update({k: torch.ones_like(d["P"]) for k in "ABFG"})
     xy, xy30 = (kp.astro_model(**s, prec="fp64", opts=o).cpu().numpy() for o in (None, {"fixed_iter": 30}))
     assert np.array_equal(np.isnan(xy), np.isnan(xy30)) and np.isnan(xy).any()
+
+
+@pytest.mark.parametrize("n_obs", [3, 70, 200])
+@pytest.mark.parametrize("call", ["grad", "nll", "gn"])
+@pytest.mark.parametrize("opts", [None, {"fixed_iter": 30}])
+def test_derivatives_at_the_epoch(call, n_obs, opts):
+    """All observations at the epoch: nothing depends on P, so every output is the one for P = 1 and the
+    derivative by P is zero."""
+    f = {"grad": kp.rv_chisq_grad, "nll": kp.rv_nll_grad, "gn": kp.rv_chisq_gn}[call]
+    rng = np.random.default_rng(3)
+    obs = dict(v=_gpu(rng.normal(0.0, 30.0, n_obs)), sigma=_gpu(rng.uniform(1.0, 5.0, n_obs)))
+    tiny, one = (f(**_args(P, 0.4, np.zeros(n_obs)), **obs, prec="fp64", opts=opts)
+                 for P in (np.array(TINY), np.ones(len(TINY))))
+    for a, b in zip(tiny, one):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
+    assert (tiny[1][0] == 0).all() and (tiny[1][1] != 0).all()
