@@ -251,8 +251,6 @@ k_demc_half(DenseArgs a, DemcArgs m, int h, int W)
             }
         }
     }
-    if constexpr (Pol::kTables >= 1)
-        if (blockIdx.x >= a.bt.n_batches) start_table_end();    // a block without a batch lets the table land
 }
 
 template <class Pol, bool JIT>
@@ -271,7 +269,9 @@ static hipError_t launch_demc_half_t(DemcArgs m, DenseArgs a, int h, LaunchShape
     const size_t rec = sizeof(typename Pol::Rec);
     const size_t table = (Pol::kTables >= 1 ? sizeof(kep_start_tab) : 0) + (Pol::kTables == 2 ? kSc64Bytes : 0);
     auto lds_of = [&](int64_t sb) { return demc_lds(W, (int)sb, a.n_pl, m.d, rec) + table; };
-    // the batch leaves room for the blocks that the registers allow (four wavefronts per SIMD)
+    // the batch leaves room for the blocks that the registers allow (four wavefronts per SIMD;
+    // two blocks of eight wavefronts: up to 80 KiB of dynamic LDS each, of the 160 KiB that a
+    // block may have)
     const int blocks = 16 / (T * W) > 8 ? 8 : 16 / (T * W);
     int64_t sb_cap = 16 * T;
     while (sb_cap > 1 && (int64_t)lds_of(sb_cap) > lds_budget(blocks > 1 ? blocks : 1)) --sb_cap;
