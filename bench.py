@@ -637,7 +637,7 @@ def main():
                 "two_rv_chisq_calls_ms": 2 * ms_c, "acceptance": acc,
                 # the chi-square part only (the dense formulation per triple); the
                 # proposal draws and the acceptance are not counted
-                "roofline": roofline_entry(f"k_demc_half<PolMixed,{(w1.t.size + 63) // 64}>",
+                "roofline": roofline_entry("k_demc_half<PolMixed,2,false>",
                                            mixed_op_classes(w1.n_pl, *op_fractions(
                                                x0[:, 2 * w1.n_pl:3 * w1.n_pl, :])), tri_gen, best / ng)}
             s.close()

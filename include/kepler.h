@@ -301,10 +301,11 @@ kep_status rv_chisq_ragged_direct(kep_plan *plan, double *chi2, void *stream);
    capture, tight serving loops, harnesses that forbid allocation): the
    chi-square of a ragged batch in one call, without a plan.  Allocates
    nothing (no hipMalloc, hipFree or allocating library call) and does not
-   synchronise: three kernels on `stream`.  The first two check each system's
+   synchronise: three kernels on `stream`, two up to 8,192 systems.  All but
+   the last check each system's
    offsets on the device and write the work order (systems by decreasing
    planet count, index order within a count, so results are the same on every
-   call) into a static device work area of the library; the third is the
+   call) into a static device work area of the library; the last is the
    plan's persistent kernel at a fixed launch shape (256-thread blocks or
    opts->block_threads, 16 systems per work item).
    Arguments as kep_plan_ragged plus chi2[n_sys] (caller-owned device array).

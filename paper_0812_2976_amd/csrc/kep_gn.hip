@@ -337,7 +337,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
             RecGrad r;
             if (!grad_setup_rec(a.fixed_iter, a.P[p], a.K[p], a.e[p], a.w[p], a.M0[p], r)) sysbad[sq] = 1;
             // the column factors 2 pi K/P and K as the binary32 pair that the rows use (read as
-            // binary64 and converted for every chunk: 262,144 x 4 x 256 1.83 against 1.81 ms)
+            // binary64 and converted for every chunk: 262,144 x 4 x 256 1.822 against 1.815 ms)
             r.fP = __hiloint2double(__float_as_int((float)r.fK), __float_as_int((float)r.fP));
             recs[sq * NPL + j] = r;
         }
@@ -545,7 +545,7 @@ template <bool ROOT, int NPL>
 hipError_t launch_gn64_t(DenseArgs a, double *jtwr, double *jtwj, LaunchShape shape, hipStream_t st)
 {
     // four wavefronts a block while their tiles and the knots leave three blocks a
-    // CU its 160 KiB (up to four planets), else two
+    // CU its 160 KiB (up to three planets; four without the knots), else two
     const size_t per_wave = gn64_lds_per_wave<NPL>(), knots = ROOT ? kSc64Bytes : 0;
     const int wpb = shape.block > 0 ? shape.block / 64 : (4 * per_wave + knots <= 53 * 1024 ? 4 : 2);
     const size_t lds = (size_t)wpb * per_wave + knots;

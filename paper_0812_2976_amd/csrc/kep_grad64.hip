@@ -9,7 +9,8 @@
 // predecessor had it, 2,000 systems are 32 wavefronts on 1,024 SIMDs and every
 // lane walks all observations one after another (2,000 x 2 x 75: 1.48 ms, of
 // which thirty Danby steps a solve were 0.97); here the same batch is 2,000
-// wavefronts of two groups each.  What bounds a large batch is VALU issue.
+// wavefronts of one group of two chunks each.  What bounds a large batch is VALU
+// issue.
 #include <hip/hip_runtime.h>
 
 #include "kep_device.h"

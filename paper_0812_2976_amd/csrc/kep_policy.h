@@ -126,7 +126,8 @@ __device__ __forceinline__ void load_start_table(uint32_t *dst)
 }
 
 // Knot of |M| and its fraction for mscale = knots / pi.  M is the centred phase
-// (|M| <= binary32 pi, so j <= knots) or NaN; v_cvt_i32_f32 turns a NaN into 0
+// (|M| <= binary32 pi, or 3.1416 from centre_angle and centre_turns, so
+// j <= knots) or NaN; v_cvt_i32_f32 turns a NaN into 0
 // (an IEEE-undefined conversion in C++, hence the instruction itself), so the
 // two words j, j + 1 read after it stay inside the row of knots + 2 words
 // without a clamp.
