@@ -251,6 +251,11 @@ k_demc_half(DenseArgs a, DemcArgs m, int h, int W)
             }
         }
     }
+    // A block without a batch lets the table land.  The launch makes none (its grid is at
+    // most the number of batches), but without this way out the compiler orders the kernel
+    // so that 32 generations of 2 x 2,048 chains x 4 x 256 take 822 us, not 808.
+    if constexpr (Pol::kTables >= 1)
+        if (blockIdx.x >= a.bt.n_batches) start_table_end();
 }
 
 template <class Pol, bool JIT>
