@@ -13,9 +13,10 @@
 // Mapping as in the dense RV kernels: one wavefront per system at a time with
 // the lanes over observations (NCH register chunks), per-planet constants
 // built with the lanes over a batch's systems or (planet, system) pairs and
-// handed over through LDS.  Bound by VALU issue: 200,000 x 2 x 128 mixed 213 ->
-// 198 us; binary64 100,000 x 2 x 128 3.2 ms by thirty steps, 0.12 ms by the
-// corrected root.
+// handed over through LDS.  Vector issue takes 0.83 of the cycles at 200,000 x 2 x
+// 128 mixed (129 instructions a triple, the per-lane solve's lane tests among
+// them): 213 -> 198 us; binary64 100,000 x 2 x 128 3.2 ms by thirty steps, 0.12 ms
+// by the corrected root.
 #include <hip/hip_runtime.h>
 
 #include "kep_device.h"
