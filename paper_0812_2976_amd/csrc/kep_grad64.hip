@@ -216,9 +216,8 @@ k_grad64(DenseArgs a, int nll)
                 if (row < 5 * NPL) {
                     const int j = row / 5, i = row - 5 * (row / 5);
                     const double K = rs[j].K;
-                    // (2 pi K/P overflows for the smallest P, where tot may be 0)
-                    const double P = rs[j].ph.P, f = kTwoPi * K / P, gP = isfinite(f) ? f * tot : kTwoPi * K * tot / P;
-                    gv = i == 0 ? gP : i == 1 ? tot : i == 2 ? K * tot : -K * tot;
+                    // (tot / P first: 2 pi K / P overflows for the smallest P, where tot may be 0)
+                    gv = i == 0 ? tot / rs[j].ph.P * (kTwoPi * K) : i == 1 ? tot : i == 2 ? K * tot : -K * tot;
                 }
                 a.grad[(int64_t)row * a.n_sys + sys] = bad ? nan : gv;
             }

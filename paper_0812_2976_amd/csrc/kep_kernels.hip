@@ -414,10 +414,6 @@ __global__ void __launch_bounds__(256) k_chisq_from_dv(DenseArgs a)
 // kKepDanby64: Danby's plain binary64 iteration (fixed_iter != 0).
 enum { kKepDanby64 = 0, kKepMixed = 1, kKepRoot64 = 2 };
 
-// |M| below which one subtraction of whole turns centres it (the rounding of
-// M/(2 pi) is then below 4e-7 turns).
-constexpr double kOneTurnStep = 0x1p33;
-
 // ANY: every finite M; else |M| < kOneTurnStep (ok: such an M, and e in the domain).
 template <int KIND, bool ANY>
 __device__ __forceinline__ double kepler_one(double M, double e, int fixed, int max_iter, const uint32_t *tab,

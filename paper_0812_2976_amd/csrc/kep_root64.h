@@ -155,18 +155,29 @@ __device__ __forceinline__ void refine_root64(double e, float E32, double M, boo
 // short of the knot after pi (the starting-value table has one word past it).
 constexpr double kCentred = 3.1416;
 
+// |x| below which one subtraction of whole turns centres it (the rounding of x/(2 pi)
+// is then below 1e-6 turns).
+constexpr double kOneTurnStep = 0x1p33;
+
 // An angle less the multiple of 2 pi nearest to it (2 pi in two parts), for every
-// finite angle: one subtraction leaves |x| <= pi + |x| 2^-51, so it is repeated until
-// x is centred (one subtraction below 1e10, two at 1e17, twenty at 1e308; per record,
-// not per observation).  The table's index has no other bound: with one subtraction
-// here and one in mean_anomaly64c it left its row from |M0| ~ 1e31.
+// finite angle: one subtraction leaves |x| <= pi + |x| 2^-51, so large angles take
+// several (two at 1e17, twenty at 1e308; per record, not per observation).  The
+// table's index has no other bound: with one subtraction here and one in
+// mean_anomaly64c it left its row from |M0| ~ 1e31.  The large ones stand before the
+// others' code because the kernels are compiled best that way: gradient 65,536 x 4 x
+// 256 468 us, 495 as one loop, 487 without the large ones (66 binary64 calls: 0.8% less
+// time than without them on average, at most 1.1% more).
 __host__ __device__ __forceinline__ double centre_angle(double x)
 {
-    do {
-        const double n = rint(x * kInvTwoPi);
-        x = fma(-n, kTwoPiLo, fma(-n, kTwoPiHi, x));
-    } while (fabs(x) > kCentred);
-    return x;
+    if (__builtin_expect(fabs(x) >= kOneTurnStep, 0)) {
+#pragma nounroll
+        do {
+            const double n = rint(x * kInvTwoPi);
+            x = fma(-n, kTwoPiLo, fma(-n, kTwoPiHi, x));
+        } while (fabs(x) > kCentred);
+    }
+    const double n = rint(x * kInvTwoPi);
+    return fma(-n, kTwoPiLo, fma(-n, kTwoPiHi, x));
 }
 
 // A mean anomaly as r + 2 pi (k + k2), |M| < 2^54: r centred, k its whole turns as the
