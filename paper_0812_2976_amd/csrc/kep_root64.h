@@ -16,8 +16,8 @@
 // instructions a triple), about 60 binary64 and 45 binary32 ones in the
 // formulation where thirty steps with library sine, cosine and three quotients
 // each took ~4000.  Measured, thirty steps -> this root: chi-square 65,536 x 4 x
-// 256 8.53 ms -> 222 us, gradient 65,536 x 4 x 256 10.0 ms -> 474 us, Gauss-Newton
-// products 32,768 x 4 x 256 6.04 ms -> 432 us, Kepler's equation alone for
+// 256 8.53 ms -> 222 us, gradient 65,536 x 4 x 256 10.0 ms -> 468 us, Gauss-Newton
+// products 32,768 x 4 x 256 6.04 ms -> 410 us, Kepler's equation alone for
 // 4,194,301 pairs 479 -> 25 us (a copy of those bytes takes 20).  Against the
 // extended-precision oracle its errors are the smaller ones (E rms 6.0e-17
 // against 9.9e-17 at e < 0.9, 9.0e-17 against 1.22e-16 up to 0.99).
